@@ -270,6 +270,29 @@ static int check_size(const ils_plan* plan, int H, int W, int C) {
   return ILS_OK;
 }
 
+// kappa and the scale s of the iterate (see FrameDesc); d.H and d.W are set.
+// A rounding error of s / (2 H W) times 1 / s would scale the whole result,
+// so 1 / s is taken among the floats within three units in the last place of
+// it, where that product is nearest to 1 / (2 H W).
+static void set_scale(FrameDesc& d, double kappa, double s) {
+  const double hw2 = 2.0 * (double)d.H * (double)d.W;
+  float c = (float)(1.0 / s);
+  for (int i = 0; i < 3; ++i) c = std::nextafter(c, 0.0f);
+  double best = HUGE_VAL;
+  for (int i = -3; i <= 3; ++i, c = std::nextafter(c, HUGE_VALF)) {
+    const float col = (float)(1.0 / (hw2 * (double)c));
+    const double off = std::fabs((double)col * (double)c * hw2 - 1.0);
+    if (off < best) {
+      best = off;
+      d.u_unscale = c;
+      d.col_scale = col;
+    }
+  }
+  d.kappa = (float)kappa;
+  d.u_scale = (float)(1.0 / (double)d.u_unscale);
+  d.kappa_mu = (float)(kappa * (double)d.u_unscale);
+}
+
 // Fill a descriptor for one frame; the caller sets f/u0/out and the
 // spectrum pointers.
 static void fill_desc_on(const char* tables, const std::map<int, LenTables>& tab, FrameDesc& d, int H, int W,
@@ -289,11 +312,9 @@ static void fill_desc_on(const char* tables, const std::map<int, LenTables>& tab
   d.W = W;
   d.C = C;
   d.ldS = spec_ld(W);
-  d.kappa = (float)((double)lambda * c0 / 2.0);
   d.a_exp = (float)((double)p / 2.0 - 1.0);
-  d.inv_eps = (float)(1.0 / (double)eps);
   d.log2_r = 0.0f;
-  d.col_scale = (float)(1.0 / (2.0 * (double)H * (double)W));
+  set_scale(d, (double)lambda * c0 / 2.0, 1.0 / std::sqrt((double)eps));
   d.boost = 0.0f;
   d.nb_row = 0;
 }
@@ -302,15 +323,16 @@ static void fill_desc(const ils_plan* plan, FrameDesc& d, int H, int W, int C, f
 }
 
 // Welsch penalty (Sec. 5): c = c0 = 2 (Eq. (20)), so kappa = lambda; the
-// pointwise step takes w = -log2(e) / (2 gamma^2).
+// iterate's scale makes exp(-g^2 / (2 gamma^2)) a power of two of -(s g)^2.
+// s is kept within 2^-60 .. 2^60: beyond, gamma is so far from any image's
+// differences that mu is 0 (or the difference itself) either way.
 static void fill_desc_welsch(const ils_plan* plan, FrameDesc& d, int H, int W, int C, float lambda,
                              float gamma) {
   fill_desc(plan, d, H, W, C, 1.0f, 1.0f, 1.0f);
-  const double g = (double)gamma;
-  d.kappa = lambda;
-  d.a_exp = (float)(-1.4426950408889634 / (2.0 * g * g));
-  d.inv_eps = 0.0f;
+  const double w = std::sqrt(1.4426950408889634 / 2.0) / (double)gamma;
+  d.a_exp = 0.0f;
   d.log2_r = 0.0f;
+  set_scale(d, (double)lambda, std::min(std::max(w, std::ldexp(1.0, -60)), std::ldexp(1.0, 60)));
 }
 
 // Tables of every compiled length, computed in double and rounded once to
@@ -408,9 +430,20 @@ static WorkList one_frame(const FrameDesc& d, int items) {
 static int row_items(const RowVariant* v, int mode, const FrameDesc& d) {
   return d.C * ilsk::row_bands(d, v->rows[mode]);
 }
-static int col_items(const ColVariant* v, const FrameDesc& d) {
-  const int s = v->cols;
-  return d.C * ((d.W / 2 + 1 + s - 1) / s);
+static int col_items(const ColVariant* v, const FrameDesc& d) { return d.C * ilsk::col_tiles(d, v->cols); }
+
+// Copy all bins of a half spectrum between its rows in the workspace (d's
+// layout; the runtime-length passes': bin k at k) and packed rows of W/2+1.
+static hipError_t copy_bins(const FrameDesc& d, bool generic, cf* ws, cf* packed, bool to_ws, hipStream_t st) {
+  const int M = d.W / 2, lo = generic ? M + 1 : M / 2 + 1, up0 = M - M / 2;
+  auto part = [&](int pos, int bin, int n) {
+    const size_t ldw = (size_t)d.ldS * sizeof(cf), ldp = (size_t)(M + 1) * sizeof(cf), rows = (size_t)d.C * d.H;
+    return to_ws ? hipMemcpy2DAsync(ws + pos, ldw, packed + bin, ldp, n * sizeof(cf), rows, hipMemcpyDeviceToDevice, st)
+                 : hipMemcpy2DAsync(packed + bin, ldp, ws + pos, ldw, n * sizeof(cf), rows, hipMemcpyDeviceToDevice, st);
+  };
+  hipError_t e = part(0, 0, lo);
+  if (e == hipSuccess && !generic) e = part(up0 + d.ldS - 1 - M, up0, M - up0 + 1);
+  return e;
 }
 
 // Elementwise kernels of the luminance mode (ils_apps.hip).
@@ -635,7 +668,7 @@ static hipError_t enqueue_persist(ils_plan* plan, const ilsk::PersistOps* fo, co
   fl.N = N;
   fl.first = first;
   fl.nb_row = (one.H + fo->rows - 1) / fo->rows;
-  fl.nb_col = (one.W / 2 + 1 + fo->cols - 1) / fo->cols;
+  fl.nb_col = ilsk::col_tiles(one, fo->cols);
   fl.wait_ticks = plan->wait_ticks;
   const long long items = channels * ((N + 1LL) * fl.nb_row + (long long)N * fl.nb_col);
   const long long grid = std::min<long long>(items, (long long)per_cu * plan->cus);
@@ -952,7 +985,7 @@ int ils_iterate_from_c(ils_plan* plan, const float* f, const float* u0, int H, i
   fill_desc(plan, d, H, W, C, lambda, p, eps);
   // c within float rounding of c0 is c0 itself (the default path, bit for bit)
   if (std::fabs((double)c - c0) > 1e-6 * c0) {
-    d.kappa = (float)((double)lambda * (double)c / 2.0);
+    set_scale(d, (double)lambda * (double)c / 2.0, 1.0 / std::sqrt((double)eps));
     d.log2_r = (float)std::log2(c0 / (double)c);
   }
   d.f = f;
@@ -1313,7 +1346,7 @@ int ils_smooth_batch(ils_plan* plan, const ils_frame* frames, int n) {
       const int sc = L.pk.cv->cols;
       srow.push_back(srow.back() + d.C * ((d.H + gr - 1) / gr));
       sfin.push_back(sfin.back() + d.C * ((d.H + gf - 1) / gf));
-      scol.push_back(scol.back() + d.C * ((d.W / 2 + 1 + sc - 1) / sc));
+      scol.push_back(scol.back() + d.C * ilsk::col_tiles(d, sc));
     }
     offs.push_back(put(cd.data(), cd.size() * sizeof(FrameDesc)));
     offs.push_back(put(srow.data(), srow.size() * sizeof(int)));
@@ -1621,12 +1654,10 @@ int ils_debug_rhs_spectrum(ils_plan* plan, const float* f, const float* u0, int 
   d.specB = reinterpret_cast<cf*>(base + (size_t)C * H * d.ldS * sizeof(cf));
   // the runtime-length first pass writes the second half spectrum
   const RowVariant* v = default_pick(H, W).rv;
-  const cf* res = frame_generic(H, W) ? d.specB : d.specA;
+  cf* res = frame_generic(H, W) ? d.specB : d.specA;
   hipError_t e = v->launch(ilsk::ROW_FIRST, ilsk::PEN_CHARBONNIER, one_frame(d, row_items(v, ilsk::ROW_FIRST, d)), plan->stream);
   if (e == hipSuccess)
-    e = hipMemcpy2DAsync(spec, (size_t)(W / 2 + 1) * sizeof(cf), res, (size_t)d.ldS * sizeof(cf),
-                         (size_t)(W / 2 + 1) * sizeof(cf), (size_t)C * H, hipMemcpyDeviceToDevice,
-                         plan->stream);
+    e = copy_bins(d, frame_generic(H, W), res, reinterpret_cast<cf*>(spec), false, plan->stream);
   return record(plan, e);
 }
 
@@ -1641,19 +1672,18 @@ int ils_debug_column_solve(ils_plan* plan, const float* spec_in, int H, int W, i
   fill_desc(plan, d, H, W, C, lambda, p, eps);
   d.f = d.u0 = nullptr;
   d.out = nullptr;
+  d.col_scale = (float)(1.0 / (2.0 * (double)H * (double)W));  // the bare solve, iterate unscaled
   char* base = plan->ws + kBatchHeaderBytes;
   d.specA = reinterpret_cast<cf*>(base);
   d.specB = reinterpret_cast<cf*>(base + (size_t)C * H * d.ldS * sizeof(cf));
-  const size_t rowb = (size_t)(W / 2 + 1) * sizeof(cf);
   // the runtime-length column pass works in place on the second half spectrum
-  cf* in = frame_generic(H, W) ? d.specB : d.specA;
-  hipError_t e = hipMemcpy2DAsync(in, (size_t)d.ldS * sizeof(cf), spec_in, rowb, rowb,
-                                  (size_t)C * H, hipMemcpyDeviceToDevice, plan->stream);
+  const bool gen = frame_generic(H, W);
+  cf* in = gen ? d.specB : d.specA;
+  hipError_t e = copy_bins(d, gen, in, reinterpret_cast<cf*>(const_cast<float*>(spec_in)), true, plan->stream);
   const ColVariant* cv = default_pick(H, W).cv;
   if (e == hipSuccess) e = cv->launch(one_frame(d, col_items(cv, d)), plan->stream);
   if (e == hipSuccess)
-    e = hipMemcpy2DAsync(spec_out, rowb, d.specB, (size_t)d.ldS * sizeof(cf), rowb, (size_t)C * H,
-                         hipMemcpyDeviceToDevice, plan->stream);
+    e = copy_bins(d, gen, d.specB, reinterpret_cast<cf*>(spec_out), false, plan->stream);
   return record(plan, e);
 }
 
@@ -1666,12 +1696,12 @@ int ils_debug_row_inverse(ils_plan* plan, const float* spec, int H, int W, int C
   fill_desc(plan, d, H, W, C, 1.0f, 1.0f, 1e-4f);
   d.f = d.u0 = nullptr;
   d.out = out;
+  d.u_unscale = 1.0f;
   char* base = plan->ws + kBatchHeaderBytes;
   d.specA = reinterpret_cast<cf*>(base + (size_t)C * H * d.ldS * sizeof(cf));
   d.specB = reinterpret_cast<cf*>(base);
-  const size_t rowb = (size_t)(W / 2 + 1) * sizeof(cf);
-  hipError_t e = hipMemcpy2DAsync(d.specB, (size_t)d.ldS * sizeof(cf), spec, rowb, rowb, (size_t)C * H,
-                                  hipMemcpyDeviceToDevice, plan->stream);
+  hipError_t e = copy_bins(d, frame_generic(H, W), d.specB, reinterpret_cast<cf*>(const_cast<float*>(spec)), true,
+                           plan->stream);
   const RowVariant* v = default_pick(H, W).rv;
   if (e == hipSuccess) e = v->launch(ilsk::ROW_FINAL, ilsk::PEN_CHARBONNIER, one_frame(d, row_items(v, ilsk::ROW_FINAL, d)), plan->stream);
   return record(plan, e);

@@ -27,8 +27,13 @@ struct cf;
 
 // One frame (all of its channels) of one ILS call.  Layouts:
 //   f, u0, out : C x H x W float32, row-major, channel stride H*W
-//   specA/specB: C x H x ldS complex64 (half spectrum, W/2+1 used columns
-//                per row, ldS >= W/2+1), channel stride H*ldS
+//   specA/specB: C x H x ldS complex64, channel stride H*ldS, ldS = M + 1
+//                rounded up to 16 (M = W/2).  Bins k <= M/2 of a row sit at
+//                k; bins k >= M - M/2 at k + ldS - 1 - M, so that both ends
+//                of a row are whole 128-byte lines and the pairs (k, M-k) of
+//                the real-FFT steps are read and written line by line from
+//                both ends (bin M/2 of an even M is held twice).  The
+//                runtime-length passes keep bin k at k.
 // The row passes read specB and write specA; the column pass reads specA
 // and writes specB.
 struct FrameDesc {
@@ -46,10 +51,15 @@ struct FrameDesc {
   const float* sy;    // 4 sin^2(pi l / H), l < H
   int H, W, C, ldS;
   float kappa;      // lambda * c / 2, c >= c0 = p eps^(p/2 - 1) (Welsch: c = 2)
-  float a_exp;      // p/2 - 1 (Welsch: -log2(e) / (2 gamma^2))
-  float inv_eps;    // 1 / eps (Welsch: unused)
+  // Between passes the iterate is kept as s u, s = eps^(-1/2) (Welsch: s =
+  // sqrt(log2(e) / 2) / gamma), so that the penalty's argument g^2 / eps is
+  // the square of a difference as it stands.
+  float u_scale;    // s
+  float u_unscale;  // 1 / s, applied by the final pass
+  float kappa_mu;   // kappa / s: weight of D^T mu(s u) in the right-hand side
+  float a_exp;      // p/2 - 1 (Welsch: unused)
   float log2_r;     // log2(c0 / c): 0 for the paper's c = c0
-  float col_scale;  // 1 / (2 H W): inverse-transform normalisation (and the
+  float col_scale;  // s / (2 H W): inverse-transform normalisation (and the
                     // factor 2 the row R2C leaves in its output)
   float boost;      // final pass writes u + boost (f - u) when non-zero
                     // (detail enhancement); 0 writes u
@@ -66,6 +76,15 @@ __host__ __device__ inline int row_bands(const FrameDesc& d, int G) {
   const int nb = d.nb_row > lo ? d.nb_row : lo;
   return nb < d.H ? nb : d.H;
 }
+
+// Bin held at position pos of a spectrum row, or -1 (see FrameDesc).
+__host__ __device__ inline int spec_bin(int pos, int M, int ldS) {
+  const int up = pos - (ldS - 1 - M);
+  return pos <= M / 2 ? pos : (up >= M - M / 2 && up <= M) ? up : -1;
+}
+
+// Column tiles of S spectrum positions per channel.
+__host__ __device__ inline int col_tiles(const FrameDesc& d, int S) { return (d.ldS + S - 1) / S; }
 
 // ROW_FIRST_SAME is the first pass when u^0 and f are the same image (the
 // data term is then read once, as u^0).

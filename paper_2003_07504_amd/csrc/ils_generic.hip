@@ -107,13 +107,14 @@ __global__ void __launch_bounds__(kGenThreads) k_gen_rhs(WorkList wl) {
   const ILS_G float* uu = u + (size_t)wrap(y - 1, H) * W;
   const ILS_G float* ud = u + (size_t)wrap(y + 1, H) * W;
   const ILS_G float* fr = gm(d.f) + (size_t)ch * H * W + (size_t)y * W;
-  const float a_exp = d.a_exp, inv_eps = d.inv_eps, kappa = d.kappa, l2r = d.log2_r;
+  const float a_exp = d.a_exp, kappa = d.kappa_mu, l2r = d.log2_r;
+  const float us = FROM_A ? 1.0f : d.u_scale;  // the first half spectrum holds s u already
   auto r_at = [&](int x) {
-    const float c = uc[x];
-    const float mxl = mu_pen<PEN>(c - uc[wrap(x - 1, W)], a_exp, inv_eps, l2r);
-    const float mx0 = mu_pen<PEN>(uc[wrap(x + 1, W)] - c, a_exp, inv_eps, l2r);
-    const float myu = mu_pen<PEN>(c - uu[x], a_exp, inv_eps, l2r);
-    const float my0 = mu_pen<PEN>(ud[x] - c, a_exp, inv_eps, l2r);
+    const float c = us * uc[x];
+    const float mxl = mu_pen<PEN>(c - us * uc[wrap(x - 1, W)], a_exp, l2r);
+    const float mx0 = mu_pen<PEN>(us * uc[wrap(x + 1, W)] - c, a_exp, l2r);
+    const float myu = mu_pen<PEN>(c - us * uu[x], a_exp, l2r);
+    const float my0 = mu_pen<PEN>(us * ud[x] - c, a_exp, l2r);
     return fmaf(kappa, (mxl - mx0) + (myu - my0), fr[x]);
   };
   for (int j = threadIdx.x; j < M; j += blockDim.x) buf[0][j] = cf{r_at(2 * j), r_at(2 * j + 1)};
@@ -166,15 +167,16 @@ __global__ void __launch_bounds__(kGenThreads) k_gen_c2r(WorkList wl) {
                             : gm(reinterpret_cast<float*>(d.specA)) + (size_t)ch * 2 * H * ldS + (size_t)y * W;
   ILS_G float2* d2 = reinterpret_cast<ILS_G float2*>(dst);
   const float kb = TO_OUT ? d.boost : 0.0f;
+  const float us = TO_OUT ? d.u_unscale : 1.0f;
   if (kb != 0.0f) {
     const ILS_G float2* f2 = reinterpret_cast<const ILS_G float2*>(gm(d.f) + (size_t)ch * H * W + (size_t)y * W);
     for (int j = threadIdx.x; j < M; j += blockDim.x) {
       const float2 fv = f2[j];
-      const cf v = z[j];
+      const cf v = {us * z[j].x, us * z[j].y};
       d2[j] = make_float2(fmaf(kb, fv.x - v.x, v.x), fmaf(kb, fv.y - v.y, v.y));
     }
   } else {
-    for (int j = threadIdx.x; j < M; j += blockDim.x) d2[j] = make_float2(z[j].x, z[j].y);
+    for (int j = threadIdx.x; j < M; j += blockDim.x) d2[j] = make_float2(us * z[j].x, us * z[j].y);
   }
 }
 
@@ -189,7 +191,7 @@ __global__ void __launch_bounds__(kGenThreads) k_gen_col(WorkList wl) {
   int local;
   const FrameDesc d = resolve(wl, blockIdx.x, local);
   const int H = d.H, Wh = d.W / 2 + 1, ldS = d.ldS;
-  const int nb = (Wh + S - 1) / S;
+  const int nb = col_tiles(d, S);
   const int ch = local / nb;
   const int c0 = (local - ch * nb) * S;
   ILS_G cf* base = gm(d.specB) + (size_t)ch * H * ldS + c0;

@@ -100,7 +100,7 @@ __attribute__((amdgpu_waves_per_eu(ColCfg<P, Q, S>::WAVES))) k_col(WorkList wl) 
   __shared__ float smem[ColCfg<P, Q, S>::LDS_F];
   int local;
   const FrameDesc d = resolve(wl, blockIdx.x, local);
-  const int nb = (d.W / 2 + 1 + S - 1) / S;
+  const int nb = col_tiles(d, S);
   const int ch = local / nb;
   col_body<P, Q, S>(d, local - ch * nb, ch, smem);
 }

@@ -29,31 +29,32 @@ __device__ __forceinline__ int imax(int a, int b) { return a > b ? a : b; }
 __device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
 
 // Normalised half-quadratic variable  mu / c = g (1 - (c0/c) (1 + g^2/eps)^(p/2 - 1))
-// (Eq. (7) divided by c, c0 = p eps^(p/2-1)); base-2 log/exp on the hardware
-// transcendental unit.  l2r = log2(c0 / c) is 0 for c = c0.
-__device__ __forceinline__ float mu_ns(float g, float a_exp, float inv_eps, float l2r) {
-  float t = fmaf(g * g, inv_eps, 1.0f);
+// (Eq. (7) divided by c, c0 = p eps^(p/2-1)), for a difference h = g / sqrt(eps)
+// of the scaled iterate: returns mu / (c sqrt(eps)).  Base-2 log/exp on the
+// hardware transcendental unit.  l2r = log2(c0 / c) is 0 for c = c0.
+__device__ __forceinline__ float mu_ns(float h, float a_exp, float l2r) {
+  float t = fmaf(h, h, 1.0f);
   float pw = __builtin_amdgcn_exp2f(fmaf(a_exp, __builtin_amdgcn_logf(t), l2r));
-  return fmaf(-g, pw, g);
+  return fmaf(-h, pw, h);
 }
 
 // Welsch penalty (Sec. 5, Eqs. (18)-(20)): with c = c0 = 2 the normalised
-// variable is mu / c = g (1 - exp(-g^2 / (2 gamma^2))); w = -log2(e) / (2 gamma^2).
-__device__ __forceinline__ float mu_ns_welsch(float g, float w, float l2r) {
-  return fmaf(-g, __builtin_amdgcn_exp2f(fmaf(w, g * g, l2r)), g);
+// variable is mu / c = g (1 - exp(-g^2 / (2 gamma^2))); h = g sqrt(log2(e) / 2) / gamma.
+__device__ __forceinline__ float mu_ns_welsch(float h, float l2r) {
+  return fmaf(-h, __builtin_amdgcn_exp2f(fmaf(-h, h, l2r)), h);
 }
 
 enum Penalty : int { PEN_CHARBONNIER = 0, PEN_WELSCH = 1 };
 
-// mu / c for the penalty of the kernel instance: (a, b) = (p/2 - 1, 1/eps)
-// for the generalised Charbonnier penalty, (w, unused) for Welsch; l2r =
+// mu / c of a scaled difference for the penalty of the kernel instance: a =
+// p/2 - 1 for the generalised Charbonnier penalty (Welsch: unused); l2r =
 // log2(c0 / c).
 template <int PEN>
-__device__ __forceinline__ float mu_pen(float g, float a, float b, float l2r) {
+__device__ __forceinline__ float mu_pen(float h, float a, float l2r) {
   if constexpr (PEN == PEN_WELSCH)
-    return mu_ns_welsch(g, a, l2r);
+    return mu_ns_welsch(h, l2r);
   else
-    return mu_ns(g, a, b, l2r);
+    return mu_ns(h, a, l2r);
 }
 
 // Cross-lane moves inside a wavefront (no LDS allocation): the value of the
@@ -102,7 +103,7 @@ struct RowGeom {
   static constexpr int QP = Q | 1;           // padded exchange row (odd => conflict-free)
   static constexpr int SLOT_F = 2 * P * QP;  // floats of LDS per row slot (>= W)
   static constexpr int TAB_F = 2 * P * QP;   // twiddles exp(-2 pi i t k1 / M) at [k1][t]
-  static constexpr int NPOST = (M + 1 + T - 1) / T;  // post-process elements per lane
+  static constexpr int NPAIR = (M / 2 + 1 + T - 1) / T;  // (k, M-k) pairs per lane of the real-FFT pre/post-process
 };
 
 // LDS that co-resident workgroups of one kernel may take on a CU in all.  A
@@ -212,29 +213,90 @@ __device__ __forceinline__ cf turn_half() {
   return cf{float(w.c), float(w.s)};
 }
 
-// ---- C2R stage A' of one row (lane k1 < P): pre-process X[k], X[M-k] into
-// Z[k] = (X[k] + conj X[M-k]) + i (X[k] - conj X[M-k]) exp(i pi k / M) and
-// take the Q-point inverse DFT over k2 (k = k1 + P k2); c2r_exchange then
-// applies the twiddle exp(2 pi i t k1 / M) and writes the exchange row
-// [k1][t].
+// Element at byte offset `off` of a pointer that is the same for the whole
+// workgroup: the pointer stays in scalar registers and the address costs one
+// 32-bit register for a whole run of accesses.
+template <class E>
+__device__ __forceinline__ ILS_G E& at(ILS_G void* base, unsigned off) {
+  return *reinterpret_cast<ILS_G E*>(reinterpret_cast<ILS_G char*>(base) + off);
+}
+template <class E>
+__device__ __forceinline__ const ILS_G E& at(const ILS_G void* base, unsigned off) {
+  return *reinterpret_cast<const ILS_G E*>(reinterpret_cast<const ILS_G char*>(base) + off);
+}
+
+// Store 8 bytes at byte offset `off` of a uniform pointer.  THROUGH: written
+// through the die's L2 at once (agent scope), so that the kernel's end does
+// not wait for the write-back of a pass's worth of dirty lines: 1080p RGB
+// FIRST 19.9 -> 17.5 us, MID 25.4 -> 23.9, FINAL 12.0 -> 9.7, column (16
+// wide) 17.4 -> 15.9; 4K MID 128 -> 123.  Only for stores that fill (nearly)
+// whole lines: with column tiles of 8 or 4, half and quarter lines that the
+// L2 would have gathered, the pass gets slower (4K, 8 wide: 65 -> 68 us; 4
+// wide: 62 -> 77), so those stay ordinary stores.
+template <bool THROUGH>
+__device__ __forceinline__ void put(ILS_G void* base, unsigned off, cf v) {
+  ILS_G unsigned long long* p =
+      reinterpret_cast<ILS_G unsigned long long*>(reinterpret_cast<ILS_G char*>(base) + off);
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  if constexpr (THROUGH)
+    __hip_atomic_store(p, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else
+    *p = b;
+}
+
+// ---- C2R pre-process of one row: Z[k] = E + i O with E = X[k] + conj X[M-k],
+// O = (X[k] - conj X[M-k]) exp(i pi k / M), and Z[M-k] = conj E + i conj O.
+// Lane `lane` of the slot's T takes the pairs (k, M-k), k = lane + T i <= M/2,
+// so that each spectrum value is loaded once and a pair's sums and product
+// are formed once (8 vector instructions per value less than one value per
+// lane from two loads, for one more LDS round trip; with the same for r2c_post
+// 1080p RGB MID 27.2 -> 25.6 us, 4K 136 -> 128); Z goes to LDS in natural order.  w1 = exp(i pi lane / M).
+// base: spectrum of the channel (uniform); row: byte offset of the row; ldS
+// its length.
 template <int P, int Q>
-__device__ __forceinline__ void c2r_stage_a(const ILS_G cf* X, int k1, cf w1, cf (&v)[Q]) {
-  constexpr int M = P * Q;
+__device__ __forceinline__ void c2r_pre(const ILS_G cf* base, unsigned row, int ldS, int lane, cf w1, cf* slc) {
+  using Geo = RowGeom<P, Q>;
+  constexpr int M = Geo::M, T = Geo::T, NP = Geo::NPAIR;
+  const unsigned up = row + 8u * (unsigned)lane, dn = row + 8u * (unsigned)(ldS - 1 - lane);
+  cf a[NP], b[NP];
+  auto load = [&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    a[i] = cf(at<cf>(base + T * i, up));
+    b[i] = cf(at<cf>(base - T * i, dn));
+  };
+  auto pair = [&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    const int k = lane + T * i;
+    if (i == 0 && lane == 0) {  // DC and Nyquist bins: real parts only
+      a[i].y = 0.0f;
+      b[i].y = 0.0f;
+    }
+    const cf e = {a[i].x + b[i].x, a[i].y - b[i].y}, df = {a[i].x - b[i].x, a[i].y + b[i].y};
+    const cf wk = (i == 0) ? w1 : cmul(w1, turn_half<(long long)T * i, M>());
+    const cf o = cmul(df, wk);
+    slc[k] = cf{e.x - o.y, e.y + o.x};
+    if (i > 0 || lane > 0) slc[M - k] = cf{e.x + o.y, o.x - e.y};
+  };
+  constexpr int full = M / 2 + 1 >= T * NP ? NP : NP - 1;  // pairs every lane has
+  const bool tail = full < NP && lane + T * full <= M / 2;
+  static_for<full>(load);
+  if constexpr (full < NP) {
+    if (tail) load(std::integral_constant<int, full>{});
+  }
+  static_for<full>(pair);
+  if constexpr (full < NP) {
+    if (tail) pair(std::integral_constant<int, full>{});
+  }
+}
+
+// ---- C2R stage A' (lane k1 < P): the Q-point inverse DFT over k2 of
+// Z[k1 + P k2]; c2r_exchange then applies the twiddle exp(2 pi i t k1 / M)
+// and writes the exchange row [k1][t].
+template <int P, int Q>
+__device__ __forceinline__ void c2r_stage_a(const cf* slc, int k1, cf (&v)[Q]) {
   static_for<Q>([&](auto k2c) {
     constexpr int k2 = decltype(k2c)::value;
-    const int k = k1 + P * k2;
-    cf a = X[k];
-    cf b = X[M - k];
-    if (k2 == 0 && k1 == 0) {  // DC and Nyquist bins: real parts only
-      a.y = 0.0f;
-      b.y = 0.0f;
-    }
-    const cf bc = {b.x, -b.y};
-    const cf e = cadd(a, bc);
-    // exp(i pi k / M) = exp(i pi k1 / M) exp(i pi k2 / Q)
-    const cf wk = (k2 == 0) ? w1 : cmul(w1, turn_half<k2, Q>());
-    const cf o = cmul(csub(a, bc), wk);
-    v[k2] = {e.x - o.y, e.y + o.x};  // e + i o
+    v[k2] = slc[k1 + P * k2];
   });
   dft<Q, +1>(v);
 }
@@ -269,27 +331,32 @@ __device__ __forceinline__ void c2r_stage_b(const cf* slc, int t, cf (&z)[P]) {
 }
 
 // ---- R2C post-process of one row held in LDS in natural order Z[0..M-1]:
-// X'[k] = E - i W_2M^k D with E = Z[k] + conj Z[M-k], D = Z[k] - conj Z[M-k]
-// (X' = 2 X), k = lane + T i <= M;  W_2M^k = W_2M^lane * W_2M^(T i).
+// with E = Z[k] + conj Z[M-k], D = Z[k] - conj Z[M-k] and w = exp(-i pi k / M)
+// the spectrum values (X' = 2 X) are X'[k] = E - i w D and X'[M-k] =
+// conj(E + i w D); pairs are dealt to the lanes as in c2r_pre.
 template <int P, int Q>
-__device__ __forceinline__ void r2c_post(const cf* slc, int lane, cf wl, ILS_G cf* Xo) {
+__device__ __forceinline__ void r2c_post(const cf* slc, int lane, cf wl, ILS_G cf* base, unsigned row, int ldS) {
   using Geo = RowGeom<P, Q>;
-  constexpr int M = Geo::M, T = Geo::T;
-  // every element but the last is in range (T (NPOST - 1) <= M), so only the
-  // last one is guarded and the rest stays one basic block
+  constexpr int M = Geo::M, T = Geo::T, NP = Geo::NPAIR;
+  const unsigned up = row + 8u * (unsigned)lane, dn = row + 8u * (unsigned)(ldS - 1 - lane);
   auto one = [&](auto ic) {
     constexpr int i = decltype(ic)::value;
     const int k = lane + T * i;
-    cf A = slc[k == M ? 0 : k];
-    cf B = slc[k == 0 ? 0 : M - k];
-    B.y = -B.y;
-    const cf E = cadd(A, B), D = csub(A, B);
+    const cf A = slc[k];
+    const cf B = slc[(i == 0 && lane == 0) ? 0 : M - k];
+    const cf E = {A.x + B.x, A.y - B.y}, D = {A.x - B.x, A.y + B.y};
     const cf w = (i == 0) ? wl : cmul(wl, turn_half<-(long long)T * i, M>());
     const cf wD = cmul(D, w);
-    Xo[k] = {E.x + wD.y, E.y - wD.x};  // E - i wD
+    put<true>(base + T * i, up, cf{E.x + wD.y, E.y - wD.x});
+    put<true>(base - T * i, dn, cf{E.x - wD.y, -E.y - wD.x});
   };
-  static_for<Geo::NPOST - 1>(one);
-  if (lane + T * (Geo::NPOST - 1) <= M) one(std::integral_constant<int, Geo::NPOST - 1>{});
+  // every pair but the last of a lane is in range, so only the last one is
+  // guarded and the rest stays one basic block
+  constexpr int full = M / 2 + 1 >= T * NP ? NP : NP - 1;
+  static_for<full>(one);
+  if constexpr (full < NP) {
+    if (lane + T * full <= M / 2) one(std::integral_constant<int, full>{});
+  }
 }
 
 // --------------------------------------------------------------------------
@@ -319,7 +386,8 @@ __device__ __forceinline__ void row_body(const FrameDesc& d, int band, int ch, f
   if (!in_slot) yrow = 0;
   const bool out_slot = slot >= 1 && slot <= Gv;
   const int yout = out_slot ? y0 - 1 + slot : 0;
-  const ILS_G float2* frow = reinterpret_cast<const ILS_G float2*>(gm(d.f) + (size_t)ch * H * W + (size_t)yout * W);
+  const ILS_G float* fch = gm(d.f) + (size_t)ch * H * W;  // the channel's data term
+  const unsigned foff = 4u * (unsigned)(yout * W) + 8u * (unsigned)lane;
 
   // per-lane factors of the real-FFT twiddles (one load each, issued first)
   const cf w2lane = gm(d.tw2_row)[lane];  // exp(-i pi lane / M)
@@ -339,21 +407,26 @@ __device__ __forceinline__ void row_body(const FrameDesc& d, int band, int ch, f
   float2 ur[P];
   if constexpr (MODE == ROW_FIRST || MODE == ROW_FIRST_SAME) {
     if (in_slot && lane < Q) {  // u^0 row of this slot, all loads in flight together
-      const ILS_G float2* urow = reinterpret_cast<const ILS_G float2*>(gm(d.u0) + (size_t)ch * H * W + (size_t)yrow * W);
+      const ILS_G float* uch = gm(d.u0) + (size_t)ch * H * W;
+      const unsigned uoff = 4u * (unsigned)(yrow * W) + 8u * (unsigned)lane;
+      const float us = d.u_scale;
       float2 uv[P];
       static_for<P>([&](auto n1c) {
         constexpr int n1 = decltype(n1c)::value;
-        uv[n1] = urow[Q * n1 + lane];
+        uv[n1] = float2(at<float2>(uch + 2 * Q * n1, uoff));
       });
       if (out_slot && !f_is_u0) {
         static_for<P>([&](auto n1c) {
           constexpr int n1 = decltype(n1c)::value;
-          fv[n1] = frow[Q * n1 + lane];
+          fv[n1] = float2(at<float2>(fch + 2 * Q * n1, foff));
         });
       }
       float2* u2 = reinterpret_cast<float2*>(sl);
       static_for<P>([&](auto n1c) {
         constexpr int n1 = decltype(n1c)::value;
+        if (f_is_u0) fv[n1] = uv[n1];
+        uv[n1].x *= us;
+        uv[n1].y *= us;
         u2[Q * n1 + lane] = uv[n1];
         if constexpr (kRegRow) ur[n1] = uv[n1];
       });
@@ -362,16 +435,16 @@ __device__ __forceinline__ void row_body(const FrameDesc& d, int band, int ch, f
   } else {
     // ---- C2R of this slot's row (its loads overlap the table load)
     cf v[Q];
-    if (in_slot && lane < P) {
-      const ILS_G cf* X = gm(d.specB) + (size_t)ch * H * ldS + (size_t)yrow * ldS;
-      c2r_stage_a<P, Q>(X, lane, cf{w2lane.x, -w2lane.y}, v);
-    }
-    __syncthreads();  // twiddle table ready
+    if (in_slot)
+      c2r_pre<P, Q>(gm(d.specB) + (size_t)ch * H * ldS, 8u * (unsigned)(yrow * ldS), ldS, lane, cf{w2lane.x, -w2lane.y}, slc);
+    slot_sync<T>();
+    if (in_slot && lane < P) c2r_stage_a<P, Q>(slc, lane, v);
+    __syncthreads();  // twiddle table ready, every read of Z done
     if (in_slot && lane < P) c2r_exchange<P, Q>(v, lane, tws, slc);
     if (out_slot && lane < Q) {  // data term, in flight during stage B'
       static_for<P>([&](auto n1c) {
         constexpr int n1 = decltype(n1c)::value;
-        fv[n1] = frow[Q * n1 + lane];
+        fv[n1] = float2(at<float2>(fch + 2 * Q * n1, foff));
       });
     }
     slot_sync<T>();
@@ -399,7 +472,7 @@ __device__ __forceinline__ void row_body(const FrameDesc& d, int band, int ch, f
   if (st_slot) {
     const float2* uc = reinterpret_cast<const float2*>(sl);
     const float2* ud = reinterpret_cast<const float2*>(sl + SLOT_F);
-    const float a_exp = d.a_exp, inv_eps = d.inv_eps, kappa = d.kappa, l2r = d.log2_r;
+    const float a_exp = d.a_exp, kappa = d.kappa_mu, l2r = d.log2_r;
     if (slot >= 1) {
       // mu_x left of pair j equals mu_x right of pair j - 1.  When a slot is
       // Q lanes of one wavefront, pair j - 1 sits in the previous lane (same
@@ -425,10 +498,9 @@ __device__ __forceinline__ void row_body(const FrameDesc& d, int band, int ch, f
           rr = uc[jp];
         }
         const float2 dn = ud[j];
-        if (f_is_u0) fv[n1] = c;
-        myd[n1] = make_float2(mu_pen<PEN>(dn.x - c.x, a_exp, inv_eps, l2r), mu_pen<PEN>(dn.y - c.y, a_exp, inv_eps, l2r));
-        const float mx0 = mu_pen<PEN>(c.y - c.x, a_exp, inv_eps, l2r);
-        const float mx1 = mu_pen<PEN>(rr.x - c.y, a_exp, inv_eps, l2r);
+        myd[n1] = make_float2(mu_pen<PEN>(dn.x - c.x, a_exp, l2r), mu_pen<PEN>(dn.y - c.y, a_exp, l2r));
+        const float mx0 = mu_pen<PEN>(c.y - c.x, a_exp, l2r);
+        const float mx1 = mu_pen<PEN>(rr.x - c.y, a_exp, l2r);
         float mxl;
         if constexpr (kLaneReuse && n1 > 0) {
           const float sh = from_prev_lane(mx1);
@@ -436,7 +508,7 @@ __device__ __forceinline__ void row_body(const FrameDesc& d, int band, int ch, f
           mxl = (t == 0) ? wr : sh;
         } else {
           const int jm = (j == 0) ? M - 1 : j - 1;
-          mxl = mu_pen<PEN>(c.x - uc[jm].y, a_exp, inv_eps, l2r);
+          mxl = mu_pen<PEN>(c.x - uc[jm].y, a_exp, l2r);
         }
         mx1_prev = mx1;
         r[n1] = {fmaf(kappa, (mxl - mx0) - myd[n1].x, fv[n1].x), fmaf(kappa, (mx0 - mx1) - myd[n1].y, fv[n1].y)};
@@ -454,7 +526,7 @@ __device__ __forceinline__ void row_body(const FrameDesc& d, int band, int ch, f
         else
           c = uc[j];
         const float2 dn = ud[j];
-        myd[n1] = make_float2(mu_pen<PEN>(dn.x - c.x, a_exp, inv_eps, l2r), mu_pen<PEN>(dn.y - c.y, a_exp, inv_eps, l2r));
+        myd[n1] = make_float2(mu_pen<PEN>(dn.x - c.x, a_exp, l2r), mu_pen<PEN>(dn.y - c.y, a_exp, l2r));
       });
     }
   }
@@ -470,7 +542,7 @@ __device__ __forceinline__ void row_body(const FrameDesc& d, int band, int ch, f
   // ---- add mu_y of the row above, then stage A (P-point forward)
   if (out_slot && lane < Q) {
     const float2* mu = reinterpret_cast<const float2*>(sl - SLOT_F);
-    const float kappa = d.kappa;
+    const float kappa = d.kappa_mu;
     static_for<P>([&](auto n1c) {
       constexpr int n1 = decltype(n1c)::value;
       const float2 m = mu[Q * n1 + t];
@@ -508,7 +580,7 @@ __device__ __forceinline__ void row_body(const FrameDesc& d, int band, int ch, f
     });
   }
   slot_sync<T>();
-  if (out_slot) r2c_post<P, Q>(slc, lane, w2lane, gm(d.specA) + (size_t)ch * H * ldS + (size_t)yout * ldS);
+  if (out_slot) r2c_post<P, Q>(slc, lane, w2lane, gm(d.specA) + (size_t)ch * H * ldS, 8u * (unsigned)(yout * ldS), ldS);
 }
 
 // --------------------------------------------------------------------------
@@ -535,29 +607,31 @@ __device__ __forceinline__ void row_final_body(const FrameDesc& d, int band, int
   const cf w2lane = gm(d.tw2_row)[lane];
   for (int i = tid; i < P * Geo::QP; i += blockDim.x) tws[i] = gm(d.twm_row)[i];
   cf v[Q];
-  if (in_slot && lane < P) {
-    const ILS_G cf* X = gm(d.specB) + (size_t)ch * H * ldS + (size_t)yrow * ldS;
-    c2r_stage_a<P, Q>(X, lane, cf{w2lane.x, -w2lane.y}, v);
-  }
-  __syncthreads();  // twiddle table ready
+  if (in_slot)
+    c2r_pre<P, Q>(gm(d.specB) + (size_t)ch * H * ldS, 8u * (unsigned)(yrow * ldS), ldS, lane, cf{w2lane.x, -w2lane.y}, slc);
+  slot_sync<T>();
+  if (in_slot && lane < P) c2r_stage_a<P, Q>(slc, lane, v);
+  __syncthreads();  // twiddle table ready, every read of Z done
   if (in_slot && lane < P) c2r_exchange<P, Q>(v, lane, tws, slc);
   slot_sync<T>();
   if (in_slot && lane < Q) {
     cf z[P];
     c2r_stage_b<P, Q>(slc, lane, z);
-    ILS_G float2* orow = reinterpret_cast<ILS_G float2*>(gm(d.out) + (size_t)ch * H * W + (size_t)yrow * W);
-    const float k = d.boost;
+    ILS_G float* och = gm(d.out) + (size_t)ch * H * W;
+    const unsigned off = 4u * (unsigned)(yrow * W) + 8u * (unsigned)lane;
+    const float k = d.boost, us = d.u_unscale;
     if (k != 0.0f) {  // detail enhancement: u + k (f - u); each element is read before it is written
-      const ILS_G float2* frow = reinterpret_cast<const ILS_G float2*>(gm(d.f) + (size_t)ch * H * W + (size_t)yrow * W);
+      const ILS_G float* fch = gm(d.f) + (size_t)ch * H * W;
       static_for<P>([&](auto n1c) {
         constexpr int n1 = decltype(n1c)::value;
-        const float2 fv = frow[Q * n1 + lane];
-        orow[Q * n1 + lane] = make_float2(fmaf(k, fv.x - z[n1].x, z[n1].x), fmaf(k, fv.y - z[n1].y, z[n1].y));
+        const float2 fv = float2(at<float2>(fch + 2 * Q * n1, off));
+        const float x = us * z[n1].x, y = us * z[n1].y;
+        put<true>(och + 2 * Q * n1, off, cf{fmaf(k, fv.x - x, x), fmaf(k, fv.y - y, y)});
       });
     } else {
       static_for<P>([&](auto n1c) {
         constexpr int n1 = decltype(n1c)::value;
-        orow[Q * n1 + lane] = make_float2(z[n1].x, z[n1].y);
+        put<true>(och + 2 * Q * n1, off, cf{us * z[n1].x, us * z[n1].y});
       });
     }
   }
@@ -573,15 +647,15 @@ __device__ __forceinline__ void col_body(const FrameDesc& d, int tile, int ch, f
   using Geo = ColGeom<P, Q, S_>;
   constexpr int H = Geo::H, S = S_, KS = Geo::KS, QT = Geo::QT;
   const int ldS = d.ldS;
-  const int Wh = d.W / 2 + 1;
   const int tid = threadIdx.x;
   const int s = tid % S;
   const int j = tid / S;
-  const int c = tile * S + s;
-  const bool col_ok = c < Wh;
-  const int cc = col_ok ? c : 0;
-  const ILS_G cf* in = gm(d.specA) + (size_t)ch * H * ldS + cc;
-  ILS_G cf* out = gm(d.specB) + (size_t)ch * H * ldS + cc;
+  const int bin = spec_bin(tile * S + s, d.W / 2, ldS);
+  const bool col_ok = bin >= 0;
+  const int cc = col_ok ? tile * S + s : 0;
+  const ILS_G cf* in = gm(d.specA) + (size_t)ch * H * ldS;
+  ILS_G cf* out = gm(d.specB) + (size_t)ch * H * ldS;
+  const unsigned off = 8u * (unsigned)(j * ldS + cc);  // this lane's element of row group 0
   cf* ex = reinterpret_cast<cf*>(smem);
   cf* tws = reinterpret_cast<cf*>(smem + Geo::EX_F);  // LDS copy of the twiddle matrix
   float* syl = smem + Geo::EX_F + 2 * P * QT;          // LDS copy of Sy
@@ -604,10 +678,10 @@ __device__ __forceinline__ void col_body(const FrameDesc& d, int tile, int ch, f
   if (j < Q) {  // stage A loads first: lane n2 = j, rows Q n1 + n2
     static_for<P>([&](auto n1c) {
       constexpr int n1 = decltype(n1c)::value;
-      x[n1] = col_ok ? cf(in[(size_t)(Q * n1 + j) * ldS]) : cf{0.0f, 0.0f};
+      x[n1] = col_ok ? cf(at<cf>(in + (size_t)(Q * n1) * ldS, off)) : cf{0.0f, 0.0f};
     });
   }
-  const float sxk = gm(d.sx)[cc];
+  const float sxk = gm(d.sx)[col_ok ? bin : 0];
   if constexpr (Geo::TAB_LDS) {
     for (int i = tid; i < P * QT; i += blockDim.x) tws[i] = gtw[i];
     for (int i = tid; i < H; i += blockDim.x) syl[i] = gsy[i];
@@ -675,7 +749,7 @@ __device__ __forceinline__ void col_body(const FrameDesc& d, int tile, int ch, f
     if (col_ok) {
       static_for<P>([&](auto n1c) {
         constexpr int n1 = decltype(n1c)::value;
-        out[(size_t)(Q * n1 + j) * ldS] = x[n1];
+        put<(S_ >= 12)>(out + (size_t)(Q * n1) * ldS, off, x[n1]);
       });
     }
   }
