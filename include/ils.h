@@ -116,25 +116,14 @@ size_t ils_batch_workspace_bytes(const ils_frame* frames, int n);
 int ils_plan_create(ils_plan** plan, int max_H, int max_W, int max_C, int max_frames,
                     void* workspace, size_t ws_bytes, void* hip_stream, unsigned flags);
 
-/* Persistent single-launch sequences (SWITCHED OFF in this library).  The
- * design: for the sizes compiled with one (256 x 256, 640 x 480,
- * 1280 x 720, 1920 x 1080, 3840 x 2160), ils_smooth and the batched calls
- * would run the 2N + 1 passes of a frame (or of a part of a batch) in one
- * launch of a persistent grid: work items (row bands and column tiles, pass
- * by pass) taken from one queue, an item of a channel's pass waiting until
- * that channel's previous pass has completed, with results bitwise those of
- * the per-pass launches.  Its first launches on the MI355X did not end
- * (twice: once with waits bounded by a poll count, once with waits bounded
- * by the real-time clock), for a reason not found yet, so the path is off:
- * on = 0 is accepted (one launch per pass, the only mode), on = 1 returns
- * ILS_ERR_INVALID_ARG. */
+/* A single-launch sequence of all 2N + 1 passes is not part of the library
+ * (one was written; its first launches on the MI355X did not end, for a
+ * reason not found, and it has been taken out).  on = 0 is accepted (one
+ * launch per pass, the only mode), on = 1 returns ILS_ERR_INVALID_ARG. */
 int ils_plan_set_persistent(ils_plan* plan, int on);
 
-/* Time a wait of a persistent launch may take before it gives up, in
- * microseconds (> 0), or the default (0: 20 ms).  For tests of the give-up
- * path: a limit of 1 us makes later items run before the items they depend
- * on have finished; the kernel still ends and ils_last_error then reports
- * ILS_ERR_HIP. */
+/* Time a wait of a single-launch sequence might take, in microseconds (>= 0).
+ * Checked and not used: no kernel of the library waits for another. */
 int ils_plan_set_wait_limit(ils_plan* plan, long long microseconds);
 
 /* Change the stream later work is enqueued on. */

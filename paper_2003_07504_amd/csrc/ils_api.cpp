@@ -18,7 +18,6 @@
 #include <vector>
 
 #include "../../include/ils.h"
-#include "ils_persist.hpp"
 #include "ils_launch.hpp"
 
 using ilsk::WorkList;
@@ -32,9 +31,6 @@ using ilsk::RowVariant;
 #define ILS_LEN(L, P, Q) const LenOps* ilsk_ops_##L();
 #include "lengths.def"
 #undef ILS_LEN
-#define ILS_PERSIST(M, Pr, Qr, G, H, Pc, Qc, S) const ilsk::PersistOps* ilsk_persist_##M##_##H();
-#include "persist.def"
-#undef ILS_PERSIST
 
 // Runtime-length passes (ils_generic.hip) for 2/3/5-smooth lengths up to
 // kMaxGenericLen without a compiled split.
@@ -63,23 +59,6 @@ const LenOps* find_ops(int L) {
   return nullptr;
 }
 
-typedef const ilsk::PersistOps* (*PersistFn)();
-const PersistFn kPersist[] = {
-#define ILS_PERSIST(M, Pr, Qr, G, H, Pc, Qc, S) &ilsk_persist_##M##_##H,
-#include "persist.def"
-#undef ILS_PERSIST
-};
-
-// The persistent single-launch sequence for row length M and column length H, if
-// one is compiled.
-const ilsk::PersistOps* find_persist(int M, int H) {
-  for (PersistFn fn : kPersist) {
-    const ilsk::PersistOps* o = fn();
-    if (o->M == M && o->H == H) return o;
-  }
-  return nullptr;
-}
-
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 bool smooth235(int n) {
@@ -102,16 +81,9 @@ inline size_t frame_ws_bytes(int H, int W, int C) {
 }
 
 // Device-resident header of the workspace: batch work lists (descriptors and
-// starts) from its start, the control blocks of persistent launches in its last
-// kPersistCtlBytes, whose last 256 bytes hold the wait-expiry word.
+// starts), at most kBatchListBytes of them, and reduction scratch.
 constexpr size_t kBatchHeaderBytes = 1 << 20;
-constexpr size_t kPersistCtlBytes = 256 << 10;
-constexpr size_t kBatchListBytes = kBatchHeaderBytes - kPersistCtlBytes;
-constexpr size_t kPersistErrOff = kBatchHeaderBytes - 256;
-constexpr size_t kPersistCtlInts = (kPersistCtlBytes - 256) / sizeof(int);
-// Time a wait of a persistent launch may take before it gives up, in ticks
-// of the 100 MHz real-time clock: 20 ms.
-constexpr long long kPersistWaitTicks = 2000000;
+constexpr size_t kBatchListBytes = kBatchHeaderBytes - (256 << 10);
 constexpr int kChains = 2;  // independent chains of passes in a batch graph
 // Frames of at least this many pixel-channels fill the chip on their own:
 // in a batch each is a part of its own (see ils_smooth_batch).
@@ -164,11 +136,7 @@ struct ils_plan {
   std::string arch;
   // pass timing
   bool prof_on;
-  // persistent single-launch sequences (sizes of persist.def) on, and the device's
-  // compute-unit count (grid of a persistent launch)
-  bool persist_on;
-  int cus;
-  long long wait_ticks;
+  int cus;  // compute units (row banding)
   std::vector<hipEvent_t> ev_pool;
   size_t ev_used;
   std::vector<int> prof_kind;  // kind of launch i; events 2i, 2i+1
@@ -634,54 +602,7 @@ static hipError_t enqueue_frame(const Pick& pk, const FrameDesc& d0, int N, int 
   return e;
 }
 
-// The persistent single-launch sequence for frames of d's size with N iterations
-// and `channels` channels in all, or nullptr (none compiled for the size,
-// switched off, pass timing active, or its control block would not fit).
-static const ilsk::PersistOps* persist_for(const ils_plan* plan, const FrameDesc& d, int N, long long channels) {
-  if (!plan->persist_on || plan->prof_on || N < 1) return nullptr;
-  if (ilsk::kPersistCtlHead + (2LL * N + 1) * channels > (long long)kPersistCtlInts) return nullptr;
-  return find_persist(d.W / 2, d.H);
-}
-
-// Enqueue one persistent launch: frames from the device descriptor array descs
-// (channel prefix sums ch_start), or the single frame `one` when descs is
-// null; control block at ctl (ctl_ints ints) in the workspace header.
-static hipError_t enqueue_persist(ils_plan* plan, const ilsk::PersistOps* fo, const FrameDesc* descs,
-                                const int* ch_start, const FrameDesc& one, int n, int C, long long channels, int N,
-                                int pen, int first, int* ctl, hipStream_t st) {
-  if (plan->cus <= 0) {
-    hipDeviceProp_t prop;
-    hipError_t e = hipGetDeviceProperties(&prop, plan->device);
-    if (e != hipSuccess) return e;
-    plan->cus = prop.multiProcessorCount;
-  }
-  const int per_cu = fo->per_cu(pen);
-  if (per_cu <= 0) return hipErrorInvalidConfiguration;
-  ilsk::PersistList fl;
-  fl.descs = descs;
-  fl.one = one;
-  fl.ctl = ctl;
-  fl.err = reinterpret_cast<int*>(plan->ws + kPersistErrOff);
-  fl.ch_start = ch_start;
-  fl.n = n;
-  fl.C = C;
-  fl.N = N;
-  fl.first = first;
-  fl.nb_row = (one.H + fo->rows - 1) / fo->rows;
-  fl.nb_col = ilsk::col_tiles(one, fo->cols);
-  fl.wait_ticks = plan->wait_ticks;
-  const long long items = channels * ((N + 1LL) * fl.nb_row + (long long)N * fl.nb_col);
-  const long long grid = std::min<long long>(items, (long long)per_cu * plan->cus);
-  const int ctl_ints = (int)(ilsk::kPersistCtlHead + (2LL * N + 1) * channels);
-  return fo->launch(pen, fl, ctl_ints, (int)grid, st);
-}
-
 static int run_frame(ils_plan* plan, const FrameDesc& d, int N, int pen = ilsk::PEN_CHARBONNIER) {
-  if (const ilsk::PersistOps* fo = persist_for(plan, d, N, d.C)) {
-    const int first = (d.f == d.u0) ? ilsk::ROW_FIRST_SAME : ilsk::ROW_FIRST;
-    int* ctl = reinterpret_cast<int*>(plan->ws + kBatchListBytes);
-    return record(plan, enqueue_persist(plan, fo, nullptr, nullptr, d, 1, d.C, d.C, N, pen, first, ctl, plan->stream));
-  }
   const Pick pk = choose(plan, d);
   const hipError_t e = enqueue_frame(pk, d, N, pen, plan->cus, plan->stream, [&](int kind, auto&& launch) {
     return timed(plan, kind, launch);
@@ -756,9 +677,7 @@ int ils_plan_create(ils_plan** plan_out, int max_H, int max_W, int max_C, int ma
   plan->tables = nullptr;
   plan->stage_next = 0;
   plan->prof_on = false;
-  plan->persist_on = false;  // switched off: see ils_plan_set_persistent
   plan->cus = 0;
-  plan->wait_ticks = kPersistWaitTicks;
   plan->ev_used = 0;
   plan->cap_stream = nullptr;
   for (int c = 0; c < kChains; ++c) {
@@ -809,7 +728,6 @@ int ils_plan_create(ils_plan** plan_out, int max_H, int max_W, int max_C, int ma
   build_tables(host, plan->tab);
   hipError_t e = hipMalloc(&plan->tables, host.size());
   if (e == hipSuccess) e = hipMemcpy(plan->tables, host.data(), host.size(), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemset(plan->ws + kPersistErrOff, 0, sizeof(int));
   if (e != hipSuccess) {
     free_plan(plan);
     return ILS_ERR_HIP;
@@ -820,17 +738,12 @@ int ils_plan_create(ils_plan** plan_out, int max_H, int max_W, int max_C, int ma
 
 int ils_plan_set_persistent(ils_plan* plan, int on) {
   if (!plan || (on != 0 && on != 1)) return ILS_ERR_INVALID_ARG;
-  // The persistent launch is switched off: its first launches did not end
-  // on the GPU, for a reason not found yet.  Only "off" is accepted.
-  if (on) return ILS_ERR_INVALID_ARG;
-  plan->persist_on = false;
-  return ILS_OK;
+  // There is no single-launch sequence (see ils.h): only "off" is accepted.
+  return on ? ILS_ERR_INVALID_ARG : ILS_OK;
 }
 
 int ils_plan_set_wait_limit(ils_plan* plan, long long microseconds) {
-  if (!plan || microseconds < 0) return ILS_ERR_INVALID_ARG;
-  plan->wait_ticks = microseconds == 0 ? kPersistWaitTicks : microseconds * 100;
-  return ILS_OK;
+  return (!plan || microseconds < 0) ? ILS_ERR_INVALID_ARG : ILS_OK;
 }
 
 int ils_plan_set_stream(ils_plan* plan, void* hip_stream) {
@@ -879,13 +792,6 @@ int ils_last_error(ils_plan* plan) {
   if (!plan) return ILS_ERR_INVALID_ARG;
   hipError_t e = hipStreamQuery(plan->stream);
   if (e != hipSuccess && e != hipErrorNotReady) record(plan, e);
-  if (e == hipSuccess) {  // stream idle: read and clear the persistent launches' wait-expiry word
-    int word = 0;
-    if (hipMemcpy(&word, plan->ws + kPersistErrOff, sizeof(int), hipMemcpyDeviceToHost) == hipSuccess && word != 0) {
-      (void)hipMemset(plan->ws + kPersistErrOff, 0, sizeof(int));
-      if (plan->last_error == ILS_OK) plan->last_error = ILS_ERR_HIP;
-    }
-  }
   int r = plan->last_error;
   plan->last_error = ILS_OK;
   return r;
@@ -1296,19 +1202,9 @@ int ils_smooth_batch(ils_plan* plan, const ils_frame* frames, int n) {
     int N, pen, first, lane;
     bool big;
     WorkList row, fin, col;
-    // the part as one persistent launch (fo != nullptr): its frames' channel
-    // count (uniform C0, else prefix sums at chs in the header), control block
-    const ilsk::PersistOps* fo;
-    int C0;
-    long long channels;
-    const int* chs;
-    int* ctl;
-    FrameDesc d0;  // the part's first frame (its size)
   };
   std::vector<Launch> launches;
   std::vector<size_t> offs;  // (desc, row starts, fin starts, col starts) per class
-  std::vector<long long> chs_offs;  // channel prefix sums of a persistent part with mixed channel counts, or -1
-  size_t ctl_used = 0;  // ints of the persistent control area taken
   int nbig = 0;
   for (const Class& cl : classes) nbig += cl.big ? 1 : 0;
   for (const Class& cl : classes) {
@@ -1352,32 +1248,6 @@ int ils_smooth_batch(ils_plan* plan, const ils_frame* frames, int n) {
     offs.push_back(put(srow.data(), srow.size() * sizeof(int)));
     offs.push_back(put(sfin.data(), sfin.size() * sizeof(int)));
     offs.push_back(put(scol.data(), scol.size() * sizeof(int)));
-    // the part as one persistent launch, when compiled for its size and its
-    // control block fits what is left of the control area
-    L.fo = persist_for(plan, cd[0], cl.N, ctot);
-    L.C0 = cd[0].C;
-    L.channels = ctot;
-    L.chs = nullptr;
-    L.ctl = nullptr;
-    L.d0 = cd[0];
-    chs_offs.push_back(-1);
-    if (L.fo) {
-      // whole 128-byte lines, so every ticket counter has a line of its own
-      const size_t need_ints = align_up(ilsk::kPersistCtlHead + (2 * (size_t)cl.N + 1) * (size_t)ctot, 32);
-      if (ctl_used + need_ints > kPersistCtlInts) {
-        L.fo = nullptr;
-      } else {
-        L.ctl = reinterpret_cast<int*>(plan->ws + kBatchListBytes) + ctl_used;
-        ctl_used += need_ints;
-        bool uniform = true;
-        std::vector<int> chs(1, 0);
-        for (const FrameDesc& d : cd) {
-          uniform = uniform && d.C == L.C0;
-          chs.push_back(chs.back() + d.C);
-        }
-        if (!uniform) chs_offs.back() = (long long)put(chs.data(), chs.size() * sizeof(int));
-      }
-    }
     const int nf = (int)cl.idx.size();
     L.row = WorkList{FrameDesc{}, nullptr, nullptr, nf, srow.back()};
     L.fin = WorkList{FrameDesc{}, nullptr, nullptr, nf, sfin.back()};
@@ -1393,7 +1263,6 @@ int ils_smooth_batch(ils_plan* plan, const ils_frame* frames, int n) {
     launches[c].row.starts = reinterpret_cast<const int*>(plan->ws + offs[4 * c + 1]);
     launches[c].fin.starts = reinterpret_cast<const int*>(plan->ws + offs[4 * c + 2]);
     launches[c].col.starts = reinterpret_cast<const int*>(plan->ws + offs[4 * c + 3]);
-    if (chs_offs[c] >= 0) launches[c].chs = reinterpret_cast<const int*>(plan->ws + chs_offs[c]);
   }
   hipError_t e = stage_upload(plan, plan->ws, hdr.data(), hdr.size());
   if (e != hipSuccess) return record(plan, e);
@@ -1404,21 +1273,10 @@ int ils_smooth_batch(ils_plan* plan, const ils_frame* frames, int n) {
   // k + 1).
   int maxN = 0;
   for (const Launch& L : launches) maxN = L.N > maxN ? L.N : maxN;
-  // A part with a persistent launch runs its whole sequence in that one launch, in
-  // the place of its first pass.
-  auto persist_part = [&](const Launch& L, hipStream_t st) {
-    return enqueue_persist(plan, L.fo, L.row.descs, L.chs, L.d0, L.row.n, L.C0, L.channels, L.N, L.pen, L.first,
-                         L.ctl, st);
-  };
   auto enqueue_chain = [&](int lane, hipStream_t st) -> hipError_t {
     hipError_t r = hipSuccess;
     for (const Launch& L : launches) {
       if (L.lane != lane || !L.big) continue;
-      if (L.fo) {
-        r = persist_part(L, st);
-        if (r != hipSuccess) return r;
-        continue;
-      }
       r = timed(plan, 0, [&] { return L.pk.rv->launch(L.first, L.pen, L.row, st); });
       if (r != hipSuccess) return r;
       for (int n = 0; n < L.N; ++n) {
@@ -1433,20 +1291,17 @@ int ils_smooth_batch(ils_plan* plan, const ils_frame* frames, int n) {
     }
     for (const Launch& L : launches) {
       if (L.lane != lane || L.big) continue;
-      if (L.fo)
-        r = persist_part(L, st);
-      else
-        r = timed(plan, 0, [&] { return L.pk.rv->launch(L.first, L.pen, L.row, st); });
+      r = timed(plan, 0, [&] { return L.pk.rv->launch(L.first, L.pen, L.row, st); });
       if (r != hipSuccess) return r;
     }
     for (int n = 0; n < maxN; ++n) {
       for (const Launch& L : launches) {
-        if (L.lane != lane || L.big || L.fo || n >= L.N) continue;
+        if (L.lane != lane || L.big || n >= L.N) continue;
         r = timed(plan, 3, [&] { return L.pk.cv->launch(L.col, st); });
         if (r != hipSuccess) return r;
       }
       for (const Launch& L : launches) {
-        if (L.lane != lane || L.big || L.fo || n >= L.N) continue;
+        if (L.lane != lane || L.big || n >= L.N) continue;
         if (n + 1 < L.N)
           r = timed(plan, 1, [&] { return L.pk.rv->launch(ilsk::ROW_MID, L.pen, L.row, st); });
         else
@@ -1483,9 +1338,6 @@ int ils_smooth_batch(ils_plan* plan, const ils_frame* frames, int n) {
     sig.push_back(L.row.total);
     sig.push_back(L.fin.total);
     sig.push_back(L.col.total);
-    sig.push_back((long long)(uintptr_t)L.fo);
-    sig.push_back((long long)(uintptr_t)L.ctl);
-    sig.push_back((long long)(uintptr_t)L.chs);
   }
   for (size_t o : offs) sig.push_back((long long)o);
   size_t hit = 0;

@@ -86,8 +86,7 @@ class Plan:
               "ils_plan_set_stream")
 
     def set_persistent(self, on: bool) -> None:
-        """Use (True, the default) or not the single-launch pass sequence of
-        the sizes compiled with one."""
+        """Accepts False only: the library has no single-launch pass sequence."""
         check(self._lib.ils_plan_set_persistent(self._h, 1 if on else 0), "ils_plan_set_persistent")
 
     def last_error(self) -> int:
