@@ -589,8 +589,7 @@ static hipError_t enqueue_frame(const Pick& pk, const FrameDesc& d0, int N, int 
   const WorkList wrow = one_frame(d, row_items(pk.rv, ilsk::ROW_MID, d));
   const WorkList wfin = one_frame(d, row_items(pk.rv, ilsk::ROW_FINAL, d));
   const WorkList wcol = one_frame(d, col_items(pk.cv, d));
-  const int first = (d.f == d.u0) ? ilsk::ROW_FIRST_SAME : ilsk::ROW_FIRST;
-  hipError_t e = wrap(0, [&] { return pk.rv->launch(first, pen, wrow, st); });
+  hipError_t e = wrap(0, [&] { return pk.rv->launch(ilsk::ROW_FIRST, pen, wrow, st); });
   for (int n = 0; n < N && e == hipSuccess; ++n) {
     e = wrap(3, [&] { return pk.cv->launch(wcol, st); });
     if (e != hipSuccess) break;
@@ -1199,7 +1198,7 @@ int ils_smooth_batch(ils_plan* plan, const ils_frame* frames, int n) {
   };
   struct Launch {
     Pick pk;
-    int N, pen, first, lane;
+    int N, pen, lane;
     bool big;
     WorkList row, fin, col;
   };
@@ -1229,10 +1228,6 @@ int ils_smooth_batch(ils_plan* plan, const ils_frame* frames, int n) {
     L.big = cl.big;
     L.N = cl.N;
     L.pen = cl.pen;
-    // the first pass reads the data term as u^0 when every frame of the class has u^0 = f
-    L.first = ilsk::ROW_FIRST_SAME;
-    for (int i : cl.idx)
-      if (descs[i].u0 != descs[i].f) L.first = ilsk::ROW_FIRST;
     std::vector<FrameDesc> cd;
     std::vector<int> srow(1, 0), sfin(1, 0), scol(1, 0);
     for (int i : cl.idx) {
@@ -1277,7 +1272,7 @@ int ils_smooth_batch(ils_plan* plan, const ils_frame* frames, int n) {
     hipError_t r = hipSuccess;
     for (const Launch& L : launches) {
       if (L.lane != lane || !L.big) continue;
-      r = timed(plan, 0, [&] { return L.pk.rv->launch(L.first, L.pen, L.row, st); });
+      r = timed(plan, 0, [&] { return L.pk.rv->launch(ilsk::ROW_FIRST, L.pen, L.row, st); });
       if (r != hipSuccess) return r;
       for (int n = 0; n < L.N; ++n) {
         r = timed(plan, 3, [&] { return L.pk.cv->launch(L.col, st); });
@@ -1291,7 +1286,7 @@ int ils_smooth_batch(ils_plan* plan, const ils_frame* frames, int n) {
     }
     for (const Launch& L : launches) {
       if (L.lane != lane || L.big) continue;
-      r = timed(plan, 0, [&] { return L.pk.rv->launch(L.first, L.pen, L.row, st); });
+      r = timed(plan, 0, [&] { return L.pk.rv->launch(ilsk::ROW_FIRST, L.pen, L.row, st); });
       if (r != hipSuccess) return r;
     }
     for (int n = 0; n < maxN; ++n) {
@@ -1333,7 +1328,6 @@ int ils_smooth_batch(ils_plan* plan, const ils_frame* frames, int n) {
     sig.push_back((long long)(uintptr_t)L.pk.cv);
     sig.push_back(L.N);
     sig.push_back(L.pen);
-    sig.push_back(L.first);
     sig.push_back(L.row.n);
     sig.push_back(L.row.total);
     sig.push_back(L.fin.total);
@@ -1481,7 +1475,7 @@ int ils_enqueue_pass(ils_plan* plan, int kind, const float* f, float* out, int H
   if (kind == 3) {
     e = pk.cv->launch(one_frame(d, col_items(pk.cv, d)), plan->stream);
   } else {
-    const int mode = kind == 0 ? ilsk::ROW_FIRST_SAME : kind == 1 ? ilsk::ROW_MID : ilsk::ROW_FINAL;
+    const int mode = kind == 0 ? ilsk::ROW_FIRST : kind == 1 ? ilsk::ROW_MID : ilsk::ROW_FINAL;
     const FrameDesc db = banded(plan->cus, pk.rv, d);
     e = pk.rv->launch(mode, ilsk::PEN_CHARBONNIER, one_frame(db, row_items(pk.rv, mode, db)), plan->stream);
   }

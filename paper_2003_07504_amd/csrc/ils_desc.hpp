@@ -86,8 +86,6 @@ __host__ __device__ inline int spec_bin(int pos, int M, int ldS) {
 // Column tiles of S spectrum positions per channel.
 __host__ __device__ inline int col_tiles(const FrameDesc& d, int S) { return (d.ldS + S - 1) / S; }
 
-// ROW_FIRST_SAME is the first pass when u^0 and f are the same image (the
-// data term is then read once, as u^0).
-enum RowMode : int { ROW_FIRST = 0, ROW_MID = 1, ROW_FINAL = 2, ROW_FIRST_SAME = 3 };
+enum RowMode : int { ROW_FIRST = 0, ROW_MID = 1, ROW_FINAL = 2 };
 
 }  // namespace ilsk

@@ -253,7 +253,7 @@ LenOps make_generic_ops() {
   o.Q = 0;
   o.nrow = 1;
   o.ncol = 1;
-  o.row[0] = RowVariant{{1, 1, 1, 1}, kGenThreads, (int)(2 * kGenRowMax * sizeof(cf)), &launch_gen_row};
+  o.row[0] = RowVariant{{1, 1, 1}, kGenThreads, (int)(2 * kGenRowMax * sizeof(cf)), &launch_gen_row};
   o.col[0] = ColVariant{S, kGenThreads, (int)(2 * kGenColCf * sizeof(cf)), &launch_gen_col<S>};
   return o;
 }

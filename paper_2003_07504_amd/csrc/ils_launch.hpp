@@ -109,7 +109,7 @@ __attribute__((amdgpu_waves_per_eu(ColCfg<P, Q, S>::WAVES))) k_col(WorkList wl) 
 // length offers up to two row-band and two column-tile shapes; the plan's
 // tuner picks one of each per image size.
 struct RowVariant {
-  int rows[4];  // output rows per block for FIRST, MID, FINAL, FIRST_SAME
+  int rows[3];  // output rows per block for FIRST, MID, FINAL
   int threads, lds_bytes;
   hipError_t (*launch)(int mode, int pen, const WorkList& wl, hipStream_t st);
 };
@@ -126,26 +126,26 @@ struct LenOps {
   ColVariant col[kMaxShapes];
 };
 
+template <int P, int Q, int G, int PEN>
+void launch_row_pen(int mode, const WorkList& wl, hipStream_t st) {
+  dim3 g(wl.total), block(RowCfg<P, Q, G>::THREADS);
+  if (mode == ROW_FIRST)
+    hipLaunchKernelGGL((k_row<P, Q, G, ROW_FIRST, PEN>), g, block, 0, st, wl);
+  else
+    hipLaunchKernelGGL((k_row<P, Q, G, ROW_MID, PEN>), g, block, 0, st, wl);
+}
+
+// (A kernel per penalty: with the penalty chosen by a uniform branch inside
+// one kernel the shapes of 168 VGPRs spill, 1080p MID 24 -> 30 us.)
 template <int P, int Q, int G>
 hipError_t launch_row(int mode, int pen, const WorkList& wl, hipStream_t st) {
-  dim3 g(wl.total), block(RowCfg<P, Q, G>::THREADS);
-  if (mode == ROW_FINAL) {  // no mu in the final pass
-    hipLaunchKernelGGL((k_row<P, Q, G, ROW_FINAL, PEN_CHARBONNIER>), g, block, 0, st, wl);
-  } else if (pen == PEN_WELSCH) {
-    if (mode == ROW_FIRST_SAME)
-      hipLaunchKernelGGL((k_row<P, Q, G, ROW_FIRST_SAME, PEN_WELSCH>), g, block, 0, st, wl);
-    else if (mode == ROW_FIRST)
-      hipLaunchKernelGGL((k_row<P, Q, G, ROW_FIRST, PEN_WELSCH>), g, block, 0, st, wl);
-    else
-      hipLaunchKernelGGL((k_row<P, Q, G, ROW_MID, PEN_WELSCH>), g, block, 0, st, wl);
-  } else {
-    if (mode == ROW_FIRST_SAME)
-      hipLaunchKernelGGL((k_row<P, Q, G, ROW_FIRST_SAME, PEN_CHARBONNIER>), g, block, 0, st, wl);
-    else if (mode == ROW_FIRST)
-      hipLaunchKernelGGL((k_row<P, Q, G, ROW_FIRST, PEN_CHARBONNIER>), g, block, 0, st, wl);
-    else
-      hipLaunchKernelGGL((k_row<P, Q, G, ROW_MID, PEN_CHARBONNIER>), g, block, 0, st, wl);
-  }
+  if (mode == ROW_FINAL)  // no mu in the final pass
+    hipLaunchKernelGGL((k_row<P, Q, G, ROW_FINAL, PEN_CHARBONNIER>), dim3(wl.total), dim3(RowCfg<P, Q, G>::THREADS), 0,
+                       st, wl);
+  else if (pen == PEN_WELSCH)
+    launch_row_pen<P, Q, G, PEN_WELSCH>(mode, wl, st);
+  else
+    launch_row_pen<P, Q, G, PEN_CHARBONNIER>(mode, wl, st);
   return hipGetLastError();
 }
 
@@ -158,7 +158,7 @@ hipError_t launch_col(const WorkList& wl, hipStream_t st) {
 template <int P, int Q, int G>
 RowVariant row_variant() {
   using C = RowCfg<P, Q, G>;
-  return RowVariant{{G, G, C::GF, G}, C::THREADS, 4 * C::LDS_F, &launch_row<P, Q, G>};
+  return RowVariant{{G, G, C::GF}, C::THREADS, 4 * C::LDS_F, &launch_row<P, Q, G>};
 }
 template <int P, int Q, int S>
 ColVariant col_variant() {

@@ -395,8 +395,6 @@ __device__ __forceinline__ void row_body(const FrameDesc& d, int band, int ch, f
   for (int i = tid; i < P * Geo::QP; i += blockDim.x) tws[i] = gm(d.twm_row)[i];
 
   float2 fv[P];
-  // u^0 = f (Algorithm 1): the data term is the slot's own u row
-  constexpr bool f_is_u0 = (MODE == ROW_FIRST_SAME);
   // When a slot is Q lanes of one wavefront (Q a power of two), mu_x is
   // passed between lanes (below).  If moreover the shape leaves 256 VGPRs
   // per lane (two waves per SIMD), each lane keeps its own pairs of u in
@@ -405,7 +403,8 @@ __device__ __forceinline__ void row_body(const FrameDesc& d, int band, int ch, f
   constexpr bool kLaneReuse = (T == Q) && (T <= 32) && ((T & (T - 1)) == 0);
   constexpr bool kRegRow = kLaneReuse && row_waves<P, Q, G>() <= 2;
   float2 ur[P];
-  if constexpr (MODE == ROW_FIRST || MODE == ROW_FIRST_SAME) {
+  if constexpr (MODE == ROW_FIRST) {
+    const bool f_is_u0 = d.f == d.u0;  // Algorithm 1: the data term is the slot's own u row, read once
     if (in_slot && lane < Q) {  // u^0 row of this slot, all loads in flight together
       const ILS_G float* uch = gm(d.u0) + (size_t)ch * H * W;
       const unsigned uoff = 4u * (unsigned)(yrow * W) + 8u * (unsigned)lane;
@@ -463,8 +462,9 @@ __device__ __forceinline__ void row_body(const FrameDesc& d, int band, int ch, f
   }
 
   // ---- stencil.  mu_y of row s (from rows s, s+1) is evaluated once by
-  // slot s and handed to slot s+1 through LDS; mu_x at x-1 is re-evaluated
-  // locally.  Slot 0 (the row above the band) only supplies mu_y.
+  // slot s and handed to slot s+1 through LDS.  Slot 0 (the row above the
+  // band) only supplies mu_y; it runs the whole step all the same (its r is
+  // not used), since it shares a wavefront with slot 1 where slots are short.
   const int t = lane;
   cf r[P];
   float2 myd[P];
@@ -473,62 +473,48 @@ __device__ __forceinline__ void row_body(const FrameDesc& d, int band, int ch, f
     const float2* uc = reinterpret_cast<const float2*>(sl);
     const float2* ud = reinterpret_cast<const float2*>(sl + SLOT_F);
     const float a_exp = d.a_exp, kappa = d.kappa_mu, l2r = d.log2_r;
-    if (slot >= 1) {
+    float mx1_prev = 0.0f;
+    static_for<P>([&](auto n1c) {
+      constexpr int n1 = decltype(n1c)::value;
       // mu_x left of pair j equals mu_x right of pair j - 1.  When a slot is
       // Q lanes of one wavefront, pair j - 1 sits in the previous lane (same
       // n1) or, for lane 0, in lane Q - 1 at n1 - 1: take it from there.
       // Likewise pair j + 1 (the right neighbour's first pixel) sits in the
       // next lane, or for lane Q - 1 in lane 0 at n1 + 1 (at n1 = P - 1 that
       // is pair 0, the periodic wrap).
-      float mx1_prev = 0.0f;
-      static_for<P>([&](auto n1c) {
-        constexpr int n1 = decltype(n1c)::value;
-        const int j = Q * n1 + t;
-        const int jp = (j == M - 1) ? 0 : j + 1;
-        float2 c, rr;
-        if constexpr (kRegRow) {
-          c = ur[n1];
-          constexpr int n1n = (n1 + 1) % P;
-          const float nx = from_next_lane(c.x);
-          const float wx = from_slot_first_lane<T>(ur[n1n].x);
-          rr.x = (t == Q - 1) ? wx : nx;
-          rr.y = 0.0f;
-        } else {
-          c = uc[j];
-          rr = uc[jp];
-        }
-        const float2 dn = ud[j];
-        myd[n1] = make_float2(mu_pen<PEN>(dn.x - c.x, a_exp, l2r), mu_pen<PEN>(dn.y - c.y, a_exp, l2r));
-        const float mx0 = mu_pen<PEN>(c.y - c.x, a_exp, l2r);
-        const float mx1 = mu_pen<PEN>(rr.x - c.y, a_exp, l2r);
-        float mxl;
-        if constexpr (kLaneReuse && n1 > 0) {
-          const float sh = from_prev_lane(mx1);
-          const float wr = from_slot_last_lane<T>(mx1_prev);
-          mxl = (t == 0) ? wr : sh;
-        } else {
-          const int jm = (j == 0) ? M - 1 : j - 1;
-          mxl = mu_pen<PEN>(c.x - uc[jm].y, a_exp, l2r);
-        }
-        mx1_prev = mx1;
-        r[n1] = {fmaf(kappa, (mxl - mx0) - myd[n1].x, fv[n1].x), fmaf(kappa, (mx0 - mx1) - myd[n1].y, fv[n1].y)};
-        // batches of five positions: their LDS reads issue together, while
-        // the registers of later positions are not claimed early
-        if constexpr ((n1 + 1) % 5 == 0) __builtin_amdgcn_sched_barrier(0);
-      });
-    } else {
-      static_for<P>([&](auto n1c) {
-        constexpr int n1 = decltype(n1c)::value;
-        const int j = Q * n1 + t;
-        float2 c;
-        if constexpr (kRegRow)
-          c = ur[n1];
-        else
-          c = uc[j];
-        const float2 dn = ud[j];
-        myd[n1] = make_float2(mu_pen<PEN>(dn.x - c.x, a_exp, l2r), mu_pen<PEN>(dn.y - c.y, a_exp, l2r));
-      });
-    }
+      const int j = Q * n1 + t;
+      const int jp = (j == M - 1) ? 0 : j + 1;
+      float2 c;
+      float right;
+      if constexpr (kRegRow) {
+        c = ur[n1];
+        constexpr int n1n = (n1 + 1) % P;
+        const float nx = from_next_lane(c.x);
+        const float wx = from_slot_first_lane<T>(ur[n1n].x);
+        right = (t == Q - 1) ? wx : nx;
+      } else {
+        c = uc[j];
+        right = uc[jp].x;
+      }
+      const float2 dn = ud[j];
+      myd[n1] = make_float2(mu_pen<PEN>(dn.x - c.x, a_exp, l2r), mu_pen<PEN>(dn.y - c.y, a_exp, l2r));
+      const float mx0 = mu_pen<PEN>(c.y - c.x, a_exp, l2r);
+      const float mx1 = mu_pen<PEN>(right - c.y, a_exp, l2r);
+      float mxl;
+      if constexpr (kLaneReuse && n1 > 0) {
+        const float sh = from_prev_lane(mx1);
+        const float wr = from_slot_last_lane<T>(mx1_prev);
+        mxl = (t == 0) ? wr : sh;
+      } else {
+        const int jm = (j == 0) ? M - 1 : j - 1;
+        mxl = mu_pen<PEN>(c.x - uc[jm].y, a_exp, l2r);
+      }
+      mx1_prev = mx1;
+      r[n1] = {fmaf(kappa, (mxl - mx0) - myd[n1].x, fv[n1].x), fmaf(kappa, (mx0 - mx1) - myd[n1].y, fv[n1].y)};
+      // batches of five positions: their LDS reads issue together, while
+      // the registers of later positions are not claimed early
+      if constexpr ((n1 + 1) % 5 == 0) __builtin_amdgcn_sched_barrier(0);
+    });
   }
   __syncthreads();  // every read of u done
   if (st_slot && slot < Gv) {
