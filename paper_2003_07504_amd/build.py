@@ -29,7 +29,8 @@ COMMON = ["-O3", "-std=c++17", f"--offload-arch={ARCH}", "-fPIC", "-Wno-unused-r
 # Sources that define the fused ILS pass kernels (device code, launch shapes
 # and compiled lengths); the pass counters in profiles/ are valid while these
 # are unchanged.
-KERNEL_SOURCES = ("fft_reg.hpp", "ils_desc.hpp", "ils_launch.hpp", "ils_passes.hpp", "lengths.def")
+KERNEL_SOURCES = ("fft_reg.hpp", "ils_desc.hpp", "ils_launch.hpp", "ils_passes.hpp", "lengths.def",
+                  "lengths_more.def")
 
 
 def source_hash() -> str:
@@ -45,9 +46,10 @@ def source_hash() -> str:
     return h.hexdigest()[:16]
 
 
-def lengths():
+def lengths(name):
+    """(L, P, Q) of the ILS_LEN lines of a csrc/*.def file."""
     out = []
-    with open(os.path.join(CSRC, "lengths.def")) as fh:
+    with open(os.path.join(CSRC, name)) as fh:
         for line in fh:
             m = re.match(r"\s*ILS_LEN\((\d+),\s*(\d+),\s*(\d+)\)", line)
             if m:
@@ -79,10 +81,12 @@ def _compile(src, obj, incremental, extra=()):
 def build(jobs: int | None = None, incremental: bool = False, verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     srcs = []
-    for L, P, Q in lengths():
+    insts = [("ILS_DEFINE_LEN", x) for x in lengths("lengths.def")]
+    insts += [("ILS_DEFINE_MORE_LEN", x) for x in lengths("lengths_more.def")]
+    for macro, (L, P, Q) in sorted(insts, key=lambda v: -v[1][0]):  # longest first: they take longest to compile
         path = os.path.join(BUILD, f"inst_{L}.hip")
         text = ('#include "../csrc/ils_launch.hpp"\n'
-                f"ILS_DEFINE_LEN({L}, {P}, {Q})\n")
+                f"{macro}({L}, {P}, {Q})\n")
         if not os.path.exists(path) or open(path).read() != text:
             with open(path, "w") as fh:
                 fh.write(text)

@@ -30,6 +30,7 @@ using ilsk::RowVariant;
 // ---------------------------------------------------------------- registry
 #define ILS_LEN(L, P, Q) const LenOps* ilsk_ops_##L();
 #include "lengths.def"
+#include "lengths_more.def"
 #undef ILS_LEN
 
 // Runtime-length passes (ils_generic.hip) for 2/3/5-smooth lengths up to
@@ -40,24 +41,27 @@ namespace {
 
 constexpr int kMaxGenericLen = 4096;
 
-typedef const LenOps* (*OpsFn)();
-const OpsFn kOps[] = {
-#define ILS_LEN(L, P, Q) &ilsk_ops_##L,
+// Lengths with compiled passes, by length; those of lengths.def (tuned) have
+// shapes for the tuner to time.
+struct Registry {
+  const LenOps* ops[kMaxGenericLen + 1] = {};
+  bool tuned[kMaxGenericLen + 1] = {};
+  Registry() {
+#define ILS_LEN(L, P, Q) ops[L] = ilsk_ops_##L(), tuned[L] = true;
 #include "lengths.def"
 #undef ILS_LEN
-};
-const int kLens[] = {
-#define ILS_LEN(L, P, Q) L,
-#include "lengths.def"
+#define ILS_LEN(L, P, Q) ops[L] = ilsk_ops_##L();
+#include "lengths_more.def"
 #undef ILS_LEN
+  }
 };
-constexpr int kNumLens = sizeof(kLens) / sizeof(kLens[0]);
-
-const LenOps* find_ops(int L) {
-  for (int i = 0; i < kNumLens; ++i)
-    if (kLens[i] == L) return kOps[i]();
-  return nullptr;
+const Registry& registry() {
+  static const Registry r;
+  return r;
 }
+
+const LenOps* find_ops(int L) { return L >= 0 && L <= kMaxGenericLen ? registry().ops[L] : nullptr; }
+bool tuned_length(int L) { return L >= 0 && L <= kMaxGenericLen && registry().tuned[L]; }
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -113,7 +117,7 @@ struct ils_plan {
   int device;
   int last_error;
   char* tables;
-  std::map<int, LenTables> tab;
+  const std::map<int, LenTables>* tab;
   char* stage[kStageSlots];
   hipEvent_t stage_ev[kStageSlots];
   bool stage_used[kStageSlots];
@@ -287,7 +291,7 @@ static void fill_desc_on(const char* tables, const std::map<int, LenTables>& tab
   d.nb_row = 0;
 }
 static void fill_desc(const ils_plan* plan, FrameDesc& d, int H, int W, int C, float lambda, float p, float eps) {
-  fill_desc_on(plan->tables, plan->tab, d, H, W, C, lambda, p, eps);
+  fill_desc_on(plan->tables, *plan->tab, d, H, W, C, lambda, p, eps);
 }
 
 // Welsch penalty (Sec. 5): c = c0 = 2 (Eq. (20)), so kappa = lambda; the
@@ -303,86 +307,64 @@ static void fill_desc_welsch(const ils_plan* plan, FrameDesc& d, int H, int W, i
   set_scale(d, (double)lambda, std::min(std::max(w, std::ldexp(1.0, -60)), std::ldexp(1.0, 60)));
 }
 
-// Tables of every compiled length, computed in double and rounded once to
-// float: twiddles, real-FFT factors, the |F(nabla)|^2 eigenvalues of the
-// periodic [1,-1] kernel (Eq. (9)) and the twiddle matrices of the
-// four-step split.  Offsets into `host` (256-byte aligned) go to `tab`.
-static void build_tables(std::vector<char>& host, std::map<int, LenTables>& tab) {
-  auto put = [&](size_t bytes) {
-    size_t off = align_up(host.size(), 256);
-    host.resize(off + bytes);
-    return off;
-  };
-  for (int i = 0; i < kNumLens; ++i) {
-    const int L = kLens[i];
-    LenTables t;
-    t.tw = put(sizeof(cf) * L);
-    t.tw2 = put(sizeof(cf) * (L + 1));
-    t.sx = put(sizeof(float) * (L + 1));
-    t.sy = put(sizeof(float) * L);
-    cf* tw = reinterpret_cast<cf*>(host.data() + t.tw);
-    for (int j = 0; j < L; ++j) {
-      double a = -2.0 * M_PI * (double)j / (double)L;
-      tw[j] = cf{(float)std::cos(a), (float)std::sin(a)};
+// Tables of every supported length, computed in double and rounded once to
+// float: real-FFT factors, the |F(nabla)|^2 eigenvalues of the periodic
+// [1,-1] kernel (Eq. (9)), the vector of twiddles (runtime-length passes)
+// and for compiled lengths the twiddle matrix of the four-step split.  `tab`
+// holds offsets into `host` (256-byte aligned).  The same for every plan:
+// made once.
+struct HostTables {
+  std::vector<char> host;
+  std::map<int, LenTables> tab;
+  HostTables() {
+    auto put = [&](size_t bytes) {
+      size_t off = align_up(host.size(), 256);
+      host.resize(off + bytes);
+      return off;
+    };
+    for (int L = 2; L <= kMaxGenericLen; ++L) {
+      const LenOps* o = find_ops(L);
+      if (!o && !generic_length(L)) continue;
+      LenTables t;
+      t.tw2 = put(sizeof(cf) * (L + 1));
+      t.sx = put(sizeof(float) * (L + 1));
+      t.sy = put(sizeof(float) * L);
+      t.tw = t.twm = put(sizeof(cf) * L);
+      // rows of Q|1 entries, entry [k1][t] = exp(-2 pi i t k1 / L): lanes
+      // that walk either index hit distinct banks
+      if (o) t.twm = put(sizeof(cf) * o->P * (o->Q | 1));
+      cf* tw = reinterpret_cast<cf*>(host.data() + t.tw);
+      cf* tw2 = reinterpret_cast<cf*>(host.data() + t.tw2);
+      float* sx = reinterpret_cast<float*>(host.data() + t.sx);
+      float* sy = reinterpret_cast<float*>(host.data() + t.sy);
+      cf* twm = reinterpret_cast<cf*>(host.data() + t.twm);
+      for (int j = 0; j < L; ++j) {
+        const double a = -2.0 * M_PI * (double)j / (double)L;
+        tw[j] = cf{(float)std::cos(a), (float)std::sin(a)};
+      }
+      for (int k = 0; k <= L; ++k) {
+        const double a = -M_PI * (double)k / (double)L;
+        tw2[k] = cf{(float)std::cos(a), (float)std::sin(a)};
+        // |F(nabla)|^2 for the periodic [1,-1] kernel: 4 sin^2(pi k / n)
+        const double s = std::sin(M_PI * (double)k / (2.0 * L));
+        sx[k] = (float)(4.0 * s * s);
+      }
+      for (int l = 0; l < L; ++l) {
+        const double s = std::sin(M_PI * (double)l / (double)L);
+        sy[l] = (float)(4.0 * s * s);
+      }
+      if (o) {
+        const int Q = o->Q, QP = Q | 1;
+        for (int k1 = 0; k1 < o->P; ++k1)
+          for (int q = 0; q < QP; ++q) twm[k1 * QP + q] = q < Q ? tw[q * k1] : cf{0.0f, 0.0f};
+      }
+      tab[L] = t;
     }
-    cf* tw2 = reinterpret_cast<cf*>(host.data() + t.tw2);
-    for (int k = 0; k <= L; ++k) {
-      double a = -M_PI * (double)k / (double)L;
-      tw2[k] = cf{(float)std::cos(a), (float)std::sin(a)};
-    }
-    // |F(nabla)|^2 for the periodic [1,-1] kernel: 4 sin^2(pi k / n)
-    float* sx = reinterpret_cast<float*>(host.data() + t.sx);
-    for (int k = 0; k <= L; ++k) {
-      double s = std::sin(M_PI * (double)k / (2.0 * L));
-      sx[k] = (float)(4.0 * s * s);
-    }
-    float* sy = reinterpret_cast<float*>(host.data() + t.sy);
-    for (int l = 0; l < L; ++l) {
-      double s = std::sin(M_PI * (double)l / (double)L);
-      sy[l] = (float)(4.0 * s * s);
-    }
-    // the row transforms' twiddles as a P x (Q|1) matrix, entry [k1][t] =
-    // exp(-2 pi i t k1 / L): lanes that walk either index hit distinct banks
-    const LenOps* o = kOps[i]();
-    const int P = o->P, Q = o->Q, QP = Q | 1;
-    t.twm = put(sizeof(cf) * P * QP);
-    cf* twm = reinterpret_cast<cf*>(host.data() + t.twm);
-    tw = reinterpret_cast<cf*>(host.data() + t.tw);
-    for (int k1 = 0; k1 < P; ++k1)
-      for (int q = 0; q < QP; ++q) twm[k1 * QP + q] = q < Q ? tw[q * k1] : cf{0.0f, 0.0f};
-    tab[L] = t;
   }
-  // lengths of the runtime-length passes: the same vectors, no matrix
-  for (int L = 2; L <= kMaxGenericLen; ++L) {
-    if (!generic_length(L)) continue;
-    LenTables t;
-    t.tw = put(sizeof(cf) * L);
-    t.tw2 = put(sizeof(cf) * (L + 1));
-    t.sx = put(sizeof(float) * (L + 1));
-    t.sy = put(sizeof(float) * L);
-    t.twm = t.tw;
-    cf* tw = reinterpret_cast<cf*>(host.data() + t.tw);
-    for (int j = 0; j < L; ++j) {
-      double a = -2.0 * M_PI * (double)j / (double)L;
-      tw[j] = cf{(float)std::cos(a), (float)std::sin(a)};
-    }
-    cf* tw2 = reinterpret_cast<cf*>(host.data() + t.tw2);
-    for (int k = 0; k <= L; ++k) {
-      double a = -M_PI * (double)k / (double)L;
-      tw2[k] = cf{(float)std::cos(a), (float)std::sin(a)};
-    }
-    float* sx = reinterpret_cast<float*>(host.data() + t.sx);
-    for (int k = 0; k <= L; ++k) {
-      double sn = std::sin(M_PI * (double)k / (2.0 * L));
-      sx[k] = (float)(4.0 * sn * sn);
-    }
-    float* sy = reinterpret_cast<float*>(host.data() + t.sy);
-    for (int l = 0; l < L; ++l) {
-      double sn = std::sin(M_PI * (double)l / (double)L);
-      sy[l] = (float)(4.0 * sn * sn);
-    }
-    tab[L] = t;
-  }
+};
+static const HostTables& host_tables() {
+  static const HostTables t;
+  return t;
 }
 
 // Single-frame work lists for the three launch shapes of a frame.
@@ -446,6 +428,12 @@ static long long size_key(int H, int W, int C) {
   return ((long long)H << 48) | ((long long)W << 32) | (long long)(unsigned)C;
 }
 
+// Sizes whose shapes the tuner times; others with compiled passes take a
+// shape by rule (rule_pick).
+static bool tuned_size(int H, int W) {
+  return tuned_length(W / 2) && tuned_length(H) && (find_ops(W / 2)->nrow > 1 || find_ops(H)->ncol > 1);
+}
+
 static void load_tune_cache(ils_plan* plan) {
   const char* path = std::getenv("ILS_TUNE_CACHE");
   if (!path) return;
@@ -454,7 +442,7 @@ static void load_tune_cache(ils_plan* plan) {
   char arch[64];
   int H, W, C, g, sc;
   while (std::fscanf(fh, "%63s %d %d %d %d %d", arch, &H, &W, &C, &g, &sc) == 6) {
-    if (plan->arch != arch || !find_ops(H) || W < 2 || (W & 1) || !find_ops(W / 2)) continue;
+    if (plan->arch != arch || W < 2 || (W & 1) || !tuned_size(H, W)) continue;
     const LenOps* orow = find_ops(W / 2);
     const LenOps* ocol = find_ops(H);
     int r = -1, c = -1;
@@ -520,12 +508,39 @@ static Pick default_pick(int H, int W) {
   return Pick{&find_ops(W / 2)->row[0], &find_ops(H)->col[0]};
 }
 
-static Pick choose(ils_plan* plan, const FrameDesc& d) {
-  if (frame_generic(d.H, d.W)) return default_pick(d.H, d.W);
+// Shapes of a compiled size without timed alternatives.  Rows: the largest
+// band (balanced shorter bands of it are cut per frame).  Columns: the widest
+// tile that makes at least 0.7 blocks per compute unit, else the narrowest.
+// Measured: 1080p RGB, 16 wide (183 blocks) 15.9 us, 12 wide (246) 16.7;
+// 480p RGB, 16 / 8 / 4 wide (63 / 126 / 252 blocks) 8.4 / 7.3 / 6.5; 256 x 256
+// grey, 16 / 8 / 4 wide (9 / 18 / 36 blocks) 6.1 / 5.0 / 4.4.
+static Pick rule_pick(const FrameDesc& d, int cus) {
   const LenOps* orow = find_ops(d.W / 2);
   const LenOps* ocol = find_ops(d.H);
   Pick pk{&orow->row[0], &ocol->col[0]};
-  if (orow->nrow < 2 && ocol->ncol < 2) return pk;
+  for (int i = 1; i < orow->nrow; ++i)
+    if (orow->row[i].rows[ilsk::ROW_MID] > pk.rv->rows[ilsk::ROW_MID]) pk.rv = &orow->row[i];
+  if (cus <= 0) return pk;
+  const ColVariant* narrow = pk.cv;
+  bool found = false;
+  for (int i = 0; i < ocol->ncol_all; ++i) {
+    const ColVariant* v = &ocol->col[i];
+    if (v->cols < narrow->cols) narrow = v;
+    if (10LL * col_items(v, d) >= 7LL * cus && (!found || v->cols > pk.cv->cols)) {
+      pk.cv = v;
+      found = true;
+    }
+  }
+  if (!found) pk.cv = narrow;
+  return pk;
+}
+
+static Pick choose(ils_plan* plan, const FrameDesc& d) {
+  if (frame_generic(d.H, d.W)) return default_pick(d.H, d.W);
+  if (!tuned_size(d.H, d.W)) return rule_pick(d, plan->cus);
+  const LenOps* orow = find_ops(d.W / 2);
+  const LenOps* ocol = find_ops(d.H);
+  Pick pk{&orow->row[0], &ocol->col[0]};
   const long long key = size_key(d.H, d.W, d.C);
   auto it = plan->tuned.find(key);
   if (it == plan->tuned.end()) {
@@ -723,8 +738,8 @@ int ils_plan_create(ils_plan** plan_out, int max_H, int max_W, int max_C, int ma
     }
   }
 
-  std::vector<char> host;
-  build_tables(host, plan->tab);
+  const std::vector<char>& host = host_tables().host;
+  plan->tab = &host_tables().tab;
   hipError_t e = hipMalloc(&plan->tables, host.size());
   if (e == hipSuccess) e = hipMemcpy(plan->tables, host.data(), host.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
@@ -799,7 +814,7 @@ int ils_last_error(ils_plan* plan) {
 int ils_shape_variants(int H, int W, int* n_row, int* n_col) {
   if (!n_row || !n_col) return ILS_ERR_INVALID_ARG;
   if (!ils_size_supported(H, W)) return ILS_ERR_UNSUPPORTED_SIZE;
-  if (frame_generic(H, W)) {
+  if (!tuned_size(H, W)) {
     *n_row = *n_col = 1;
     return ILS_OK;
   }
@@ -820,7 +835,7 @@ int ils_plan_tune(ils_plan* plan, int H, int W, int C, int* row_shape, int* col_
   d.f = d.u0 = reinterpret_cast<const float*>(d.specB);
   d.out = reinterpret_cast<float*>(d.specB);
   const Pick pk = choose(plan, d);
-  if (frame_generic(H, W)) {
+  if (!tuned_size(H, W)) {
     *row_shape = *col_shape = 0;
     return ILS_OK;
   }
@@ -836,7 +851,7 @@ int ils_plan_set_shapes(ils_plan* plan, int H, int W, int C, int row_shape, int 
   int nr = 1, nc = 1;
   (void)ils_shape_variants(H, W, &nr, &nc);
   if (row_shape < 0 || row_shape >= nr || col_shape < 0 || col_shape >= nc) return ILS_ERR_INVALID_ARG;
-  if (frame_generic(H, W)) return ILS_OK;
+  if (!tuned_size(H, W)) return ILS_OK;
   plan->tuned[size_key(H, W, C)] = {row_shape, col_shape};
   return ILS_OK;
 }
@@ -1375,8 +1390,8 @@ int ils_smooth_batch(ils_plan* plan, const ils_frame* frames, int n) {
 // Device memory of ils_smooth_noalloc: the tables of every compiled length
 // (first kNoAllocTableBytes), then the two half spectra of one frame.  Each
 // GPU the library runs on holds its own copy until the process ends.
-constexpr size_t kNoAllocTableBytes = 4u << 20;
-constexpr size_t kNoAllocBytes = 64u << 20;
+constexpr size_t kNoAllocTableBytes = 6u << 20;
+constexpr size_t kNoAllocBytes = kNoAllocTableBytes + (60u << 20);
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
 namespace {
@@ -1385,7 +1400,6 @@ struct NoAllocDevice {
   bool ready;
   char* base;  // device address of `scratch` on this device
   int cus;     // compute units (row banding)
-  std::map<int, LenTables> tab;
 };
 NoAllocDevice g_noalloc[kNoAllocDevices];
 std::mutex g_noalloc_mu;
@@ -1402,16 +1416,13 @@ int noalloc_device(NoAllocDevice** out) {
   if (!nd.ready) {
     void* ptr = nullptr;
     if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return ILS_ERR_HIP;
-    std::vector<char> host;
-    std::map<int, LenTables> tab;
-    build_tables(host, tab);
+    const std::vector<char>& host = host_tables().host;
     if (host.size() > kNoAllocTableBytes) return ILS_ERR_HIP;
     if (hipMemcpy(ptr, host.data(), host.size(), hipMemcpyHostToDevice) != hipSuccess) return ILS_ERR_HIP;
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
     nd.cus = cus;
     nd.base = static_cast<char*>(ptr);
-    nd.tab = std::move(tab);
     nd.ready = true;
   }
   *out = &nd;
@@ -1442,15 +1453,15 @@ int ils_smooth_noalloc(const float* f, int H, int W, int C, float lambda, float 
   rc = noalloc_device(&nd);
   if (rc != ILS_OK) return rc;
   FrameDesc d;
-  fill_desc_on(nd->base, nd->tab, d, H, W, C, lambda, p, eps);
+  fill_desc_on(nd->base, host_tables().tab, d, H, W, C, lambda, p, eps);
   d.f = f;
   d.u0 = f;
   d.out = out;
   char* spec = nd->base + kNoAllocTableBytes;
   d.specA = reinterpret_cast<cf*>(spec);
   d.specB = reinterpret_cast<cf*>(spec + (size_t)C * H * d.ldS * sizeof(cf));
-  // default tile shapes: no tuning (timing would create events)
-  const Pick pk = default_pick(H, W);
+  // tile shapes by rule: no tuning (timing would create events)
+  const Pick pk = frame_generic(H, W) ? default_pick(H, W) : rule_pick(d, nd->cus);
   const hipError_t e =
       enqueue_frame(pk, d, N, ilsk::PEN_CHARBONNIER, nd->cus, st, [](int, auto&& launch) { return launch(); });
   return e == hipSuccess ? ILS_OK : ILS_ERR_HIP;

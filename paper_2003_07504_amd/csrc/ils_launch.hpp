@@ -105,9 +105,10 @@ __attribute__((amdgpu_waves_per_eu(ColCfg<P, Q, S>::WAVES))) k_col(WorkList wl) 
   col_body<P, Q, S>(d, local - ch * nb, ch, smem);
 }
 
-// Host-side table of one length's launchers (one block per work item).  A
-// length offers up to two row-band and two column-tile shapes; the plan's
-// tuner picks one of each per image size.
+// Host-side table of one length's launchers (one block per work item).  Of
+// its row-band and column-tile shapes the plan's tuner times the first nrow
+// and ncol; the column tiles up to ncol_all are for the rule that serves
+// sizes without timed alternatives.
 struct RowVariant {
   int rows[3];  // output rows per block for FIRST, MID, FINAL
   int threads, lds_bytes;
@@ -121,7 +122,7 @@ struct ColVariant {
 constexpr int kMaxShapes = 6;
 struct LenOps {
   int L, P, Q;
-  int nrow, ncol;
+  int nrow, ncol, ncol_all;
   RowVariant row[kMaxShapes];
   ColVariant col[kMaxShapes];
 };
@@ -174,19 +175,25 @@ void add_row(LenOps& o) {
 }
 template <int P, int Q, int S>
 void add_col(LenOps& o) {
-  for (int i = 0; i < o.ncol; ++i)
+  for (int i = 0; i < o.ncol_all; ++i)
     if (o.col[i].cols == S) return;
-  o.col[o.ncol++] = col_variant<P, Q, S>();
+  o.col[o.ncol_all++] = col_variant<P, Q, S>();
 }
-
-// Alternatives are compiled only for lengths where they can matter.  Entry 0
-// is the default shape (used when the tuner is off or cannot time).
 template <int P, int Q>
-LenOps make_ops(int L) {
+LenOps start_ops(int L) {
   LenOps o{};
   o.L = L;
   o.P = P;
   o.Q = Q;
+  return o;
+}
+
+// Timed alternatives are compiled only for lengths where they can matter;
+// shorter columns get narrower tiles for the rule.  Entry 0 is the default
+// shape (used when the tuner is off or cannot time).
+template <int P, int Q>
+LenOps make_ops(int L) {
+  LenOps o = start_ops<P, Q>(L);
   add_row<P, Q, row_band<P, Q>()>(o);
   add_col<P, Q, col_tile<P, Q>()>(o);
   if constexpr (P * Q >= 480) {
@@ -198,7 +205,24 @@ LenOps make_ops(int L) {
     add_col<P, Q, col_tile_alt<P, Q, 0>()>(o);
     add_col<P, Q, col_tile_alt<P, Q, 1>()>(o);
     add_col<P, Q, col_tile_alt<P, Q, 2>()>(o);
+    o.ncol = o.ncol_all;
+  } else {
+    o.ncol = o.ncol_all;
+    add_col<P, Q, col_tile_alt<P, Q, 1>()>(o);
+    add_col<P, Q, col_tile_alt<P, Q, 2>()>(o);
   }
+  return o;
+}
+
+// The further lengths (lengths_more.def): one row band, column tiles for the rule.
+template <int P, int Q>
+LenOps make_more_ops(int L) {
+  LenOps o = start_ops<P, Q>(L);
+  add_row<P, Q, row_band_wide<P, Q>()>(o);
+  add_col<P, Q, col_tile<P, Q>()>(o);
+  o.ncol = o.ncol_all;
+  add_col<P, Q, col_tile_alt<P, Q, 1>()>(o);
+  add_col<P, Q, col_tile_alt<P, Q, 2>()>(o);
   return o;
 }
 
@@ -208,4 +232,9 @@ LenOps make_ops(int L) {
   const ilsk::LenOps* ilsk_ops_##L() {                     \
     static const ilsk::LenOps o = ilsk::make_ops<P, Q>(L); \
     return &o;                                             \
+  }
+#define ILS_DEFINE_MORE_LEN(L, P, Q)                            \
+  const ilsk::LenOps* ilsk_ops_##L() {                          \
+    static const ilsk::LenOps o = ilsk::make_more_ops<P, Q>(L); \
+    return &o;                                                  \
   }

@@ -162,6 +162,22 @@ constexpr int row_band_alt() {
   return i == 0 ? gm : i == 1 ? (3 * gm + 2) / 4 : i == 2 ? (5 * gm + 4) / 8 : i == 3 ? 5 : 4;
 }
 
+// The band of a length with a single shape: one workgroup per CU with the
+// largest band that fits the LDS, 1024 threads and the registers (a lane
+// needs about 4 P + 28 of them in the stencil, 2 Q + 40 in the Q-point
+// stages; w waves per SIMD leave 512 / w).  Single frames cut it into
+// balanced shorter bands (ils_api.cpp), so a large one costs nothing when
+// rows are few, and few halo rows per output row when they are many.
+template <int P, int Q>
+constexpr int row_band_wide() {
+  constexpr int T = RowGeom<P, Q>::T;
+  constexpr int need = 4 * P + 28 > 2 * Q + 40 ? 4 * P + 28 : 2 * Q + 40;
+  constexpr int waves = 512 / need < 1 ? 1 : (512 / need > 4 ? 4 : 512 / need);  // per SIMD
+  int g = row_band_max<P, Q>();
+  while (g > 1 && (g + 2) * T > 256 * waves) --g;
+  return g;
+}
+
 // Column tile of S spectrum columns.  The exchange row of one k1 is padded
 // so that successive k1 groups land on different LDS banks.
 constexpr int col_ks(int Q, int S) { return (S >= 16) ? Q * S : Q * S + ((S - (Q * S) % 16) + 16) % 16; }
