@@ -54,7 +54,7 @@ inline int gchan(int i) { return kNet.L[i].co == 3 ? 8 : 32; }
 
 inline size_t al(size_t v) { return (v + 255) / 256 * 256; }
 
-constexpr int kWgradBlocks = 256;
+constexpr int kWgradBlocks = 512;
 constexpr int kLossBlocks = 256;
 
 // --------------------------------------------------------- small kernels
@@ -115,12 +115,17 @@ __global__ void __launch_bounds__(256) k_loss_grad(const float* v, const float* 
   if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
-__global__ void k_loss_final(const double* partial, int nb, double n, float* loss) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    double s = 0.0;
-    for (int i = 0; i < nb; ++i) s += partial[i];
-    *loss = (float)(s / n);
+// One block: a thread per partial, then a tree (one thread summing all of
+// them waited for a load at a time: 15 us).
+__global__ void __launch_bounds__(kLossBlocks) k_loss_final(const double* partial, double n, float* loss) {
+  __shared__ double red[kLossBlocks];
+  red[threadIdx.x] = partial[threadIdx.x];
+  __syncthreads();
+  for (int s = kLossBlocks / 2; s > 0; s >>= 1) {
+    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+    __syncthreads();
   }
+  if (threadIdx.x == 0) *loss = (float)(red[0] / n);
 }
 
 // Partial weight and bias gradients of one convolution on the MFMA units:
@@ -129,78 +134,155 @@ __global__ void k_loss_final(const double* partial, int nb, double n, float* los
 // over the 32 pixels of one tile row (one K block of v_mfma_f32_16x16x32_bf16).
 // The (16-row co block, 16-column ci block) pairs are dealt to the four
 // waves; when there are two pairs (first and last layers), two waves share a
-// pair, taking alternate tile rows, and add up through LDS at the end.  The
-// fragments are gathered from the NHWC tiles in LDS (channels beyond the
-// layer's read as zero).  db[co] = sum g[pixel][co] on the VALU.  Blocks
-// stride over TH x TW pixel tiles and write one partial row each (reduced
-// in a fixed order afterwards: deterministic).
+// pair, taking alternate tile rows, and add up through LDS at the end.
+// db[co] is one more product, with a column of ones.  Blocks stride over TH x
+// TW pixel tiles and write one partial row each (reduced in a fixed order
+// afterwards: deterministic).
+//
+// The tensors are NHWC, while both operands want eight consecutive pixels of
+// a channel per lane.  A thread loads four pixels x eight channels, turns
+// them round in registers and writes them to LDS channel by channel; a
+// fragment is then one 16-byte read, the tap one column on is the same ten
+// pixels shifted by 16 bits, and a row of x serves three rows of taps.  The
+// next tile's loads are in flight during a tile's products.  Reading
+// fragments element by element from NHWC tiles took 110 us a layer for 16
+// crops of 256 x 256 (134 MB); this takes
+// 42 us with two blocks per CU, 51 with one.
+template <int C, int ROWS, int QUADS, int ROWB>
+struct PixTile {  // ROWS x 4 QUADS pixels of C channels, held channel-major in LDS
+  static constexpr int CG = C / 8;                        // channel groups of 8
+  static constexpr int ITEMS = ROWS * QUADS * CG;         // (row, 4 pixels, 8 channels)
+  static constexpr int NIT = (ITEMS + 255) / 256;         // items per thread
+  static constexpr int CS = (ROWS * ROWB / 16 | 1) * 16;  // channel stride: an odd number of 16-byte units
+  static constexpr int BYTES = C * CS;
+  u32x4 v[NIT][4];
+
+  __device__ __forceinline__ static void place(int i, int& row, int& px, int& cg) {
+    cg = i % CG;
+    const int q = i / CG;
+    row = q / QUADS;
+    px = 4 * (q - row * QUADS);
+  }
+  // pixel (row, px) of the tile is image pixel (y0 + row, x0 + px); WRAP: periodic, else zero outside
+  template <bool WRAP>
+  __device__ __forceinline__ void fetch(const bf16* img, int H, int W, int y0, int x0) {
+#pragma unroll
+    for (int j = 0; j < NIT; ++j) {
+      const int i = imin(threadIdx.x + j * 256, ITEMS - 1);
+      int row, px, cg;
+      place(i, row, px, cg);
+      const int gy = WRAP ? wrapi(y0 + row, H) : y0 + row;
+      const int gx = x0 + px;
+      const bool rowin = gy < H;
+      const bf16* src = img + (size_t)(rowin ? gy : 0) * W * C + cg * 8;
+      if (rowin && gx >= 0 && gx + 4 <= W) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) v[j][p] = *reinterpret_cast<const u32x4*>(src + (size_t)(gx + p) * C);
+      } else {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const bool in = WRAP || (rowin && gx + p < W);
+          const u32x4 r = *reinterpret_cast<const u32x4*>(src + (size_t)(in ? wrapi(gx + p, W) : 0) * C);
+          v[j][p] = in ? r : u32x4{0, 0, 0, 0};
+        }
+      }
+    }
+  }
+  __device__ __forceinline__ void store(unsigned char* lds) const {
+#pragma unroll
+    for (int j = 0; j < NIT; ++j) {
+      const int i = threadIdx.x + j * 256;
+      if (j * 256 + 256 > ITEMS && i >= ITEMS) continue;
+      int row, px, cg;
+      place(i, row, px, cg);
+      unsigned char* dst = lds + cg * 8 * CS + row * ROWB + px * 2;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {  // channels 2 c (low halves) and 2 c + 1 (high halves)
+        *reinterpret_cast<uint2*>(dst + 2 * c * CS) =
+            make_uint2(__builtin_amdgcn_perm(v[j][1][c], v[j][0][c], 0x05040100),
+                       __builtin_amdgcn_perm(v[j][3][c], v[j][2][c], 0x05040100));
+        *reinterpret_cast<uint2*>(dst + (2 * c + 1) * CS) =
+            make_uint2(__builtin_amdgcn_perm(v[j][1][c], v[j][0][c], 0x07060302),
+                       __builtin_amdgcn_perm(v[j][3][c], v[j][2][c], 0x07060302));
+      }
+    }
+  }
+};
+
 template <int GC, int XC>
 __global__ void __launch_bounds__(256) k_wgrad_mfma(const bf16* g, const bf16* x, float* partial, int gcr, int xcr,
                                                    int B, int H, int W) {
-  constexpr int LH = TH + 2, LW = TW + 2;
   constexpr int MB = (GC + 15) / 16, NB = (XC + 15) / 16;
   constexpr int PAIRS = MB * NB;  // 2 or 4
   constexpr int RG = 4 / PAIRS;   // waves per pair
   static_assert(PAIRS * RG == 4, "four waves per block");
-  constexpr int G_BYTES = TH * TW * GC * 2, X_BYTES = LH * LW * XC * 2;
-  constexpr int RED_BYTES = 2 * 64 * 36 * 4;  // accumulators of two waves
-  constexpr int LDS_BYTES = (G_BYTES + X_BYTES) > RED_BYTES ? (G_BYTES + X_BYTES) : RED_BYTES;
-  __shared__ __attribute__((aligned(16))) unsigned char lds[LDS_BYTES];
-  __shared__ float bred[256];
-  bf16* gt = reinterpret_cast<bf16*>(lds);
-  bf16* xt = reinterpret_cast<bf16*>(lds + G_BYTES);
+  static_assert(TH == 8 && TW == 32, "one K block per tile row");
+  using GT = PixTile<GC, TH, TW / 4, 2 * TW>;
+  using XT = PixTile<XC, TH + 2, (TW + 4) / 4, 80>;  // columns x0 - 1 .. x0 + 34 (the last two are not used)
+  constexpr int RED_BYTES = 2 * 64 * 40 * 4;         // accumulators of two waves
+  constexpr int TILE_BYTES = GT::BYTES + XT::BYTES;
+  __shared__ __attribute__((aligned(16))) unsigned char lds[TILE_BYTES > RED_BYTES ? TILE_BYTES : RED_BYTES];
+  unsigned char* gl = lds;
+  unsigned char* xl = lds + GT::BYTES;
   const int tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int pair = wave % PAIRS, rg = wave / PAIRS;
   const int mb = pair / NB, nb = pair - mb * NB;
   const int m = lane & 15, kc = lane >> 4;
-  const int co_a = mb * 16 + m;   // A row of this lane
-  const int ci_b = nb * 16 + m;   // B column of this lane
-  f32x4 acc[9];
+  // channels beyond the tensor's give rows and columns that are not written
+  const unsigned char* ga = gl + ((mb * 16 + m) % GC) * GT::CS + kc * 16;
+  const unsigned char* xa = xl + ((nb * 16 + m) % XC) * XT::CS + kc * 16;
+  f32x4 acc[9], accb = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int tap = 0; tap < 9; ++tap) acc[tap] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float accb = 0.0f;
-  const int bco = tid % GC;  // bias: channel and pixel phase of this thread
-  const int bph = tid / GC;
+  const bf16x8 ones = {(bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f};
 
   const int tiles_x = (W + TW - 1) / TW, tiles_y = (H + TH - 1) / TH;
   const int ntiles = B * tiles_x * tiles_y;
   const size_t plane = (size_t)H * W;
-  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+  GT gt;
+  XT xt;
+  auto fetch = [&](int tile) {
     const int img = tile / (tiles_x * tiles_y);
     const int rem = tile - img * tiles_x * tiles_y;
     const int ty = rem / tiles_x, tx = rem - ty * tiles_x;
-    const int y0 = ty * TH, x0 = tx * TW;
-    for (int i = tid; i < TH * TW * (GC / 8); i += 256) {
-      const int pix = i / (GC / 8), chn = i - pix * (GC / 8);
-      const int py = pix / TW, px = pix - py * TW;
-      const int gy = y0 + py, gx = x0 + px;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (gy < H && gx < W) v = *reinterpret_cast<const uint4*>(&g[((size_t)img * plane + (size_t)gy * W + gx) * GC + chn * 8]);
-      *reinterpret_cast<uint4*>(&gt[pix * GC + chn * 8]) = v;
-    }
-    for (int i = tid; i < LH * LW * (XC / 8); i += 256) {
-      const int pix = i / (XC / 8), chn = i - pix * (XC / 8);
-      const int ly = pix / LW, lx = pix - ly * LW;
-      const int gy = wrapi(y0 + ly - 1, H), gx = wrapi(x0 + lx - 1, W);
-      *reinterpret_cast<uint4*>(&xt[pix * XC + chn * 8]) =
-          *reinterpret_cast<const uint4*>(&x[((size_t)img * plane + (size_t)gy * W + gx) * XC + chn * 8]);
-    }
+    gt.template fetch<false>(g + (size_t)img * plane * GC, H, W, ty * TH, tx * TW);
+    xt.template fetch<true>(x + (size_t)img * plane * XC, H, W, ty * TH - 1, tx * TW - 1);
+  };
+  if ((int)blockIdx.x < ntiles) fetch(blockIdx.x);
+  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    gt.store(gl);
+    xt.store(xl);
     __syncthreads();
-    for (int p = bph; p < TH * TW; p += 256 / GC) accb += bf2f(gt[p * GC + bco]);
-    for (int py = rg; py < TH; py += RG) {
-      bf16x8 a;
+    if (tile + (int)gridDim.x < ntiles) fetch(tile + gridDim.x);
+    // row r of x: ten pixels of this lane's channel, as the taps' three columns
+    auto xrow = [&](int r, bf16x8 (&f)[3]) {
+      const u32x4 d = *reinterpret_cast<const u32x4*>(xa + r * 80);
+      const unsigned e = *reinterpret_cast<const unsigned*>(xa + r * 80 + 16);
+      f[0] = __builtin_bit_cast(bf16x8, d);
+      f[1] = __builtin_bit_cast(bf16x8, u32x4{__builtin_amdgcn_alignbit(d[1], d[0], 16), __builtin_amdgcn_alignbit(d[2], d[1], 16),
+                                              __builtin_amdgcn_alignbit(d[3], d[2], 16), __builtin_amdgcn_alignbit(e, d[3], 16)});
+      f[2] = __builtin_bit_cast(bf16x8, u32x4{d[1], d[2], d[3], e});
+    };
+    bf16x8 xf[3][3];
+    if constexpr (RG == 1) {
+      xrow(0, xf[0]);
+      xrow(1, xf[1]);
+    }
 #pragma unroll
-      for (int e = 0; e < 8; ++e) a[e] = co_a < GC ? gt[(py * TW + kc * 8 + e) * GC + co_a] : f2bf(0.0f);
+    for (int p = 0; p < TH / RG; ++p) {
+      const int py = RG * p + rg;
+      if constexpr (RG == 1) {
+        xrow(p + 2, xf[(p + 2) % 3]);
+      } else {
 #pragma unroll
-      for (int tap = 0; tap < 9; ++tap) {
-        const int ta = tap / 3, tc = tap - 3 * ta;
-        bf16x8 b;
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          b[e] = ci_b < XC ? xt[((py + ta) * LW + kc * 8 + e + tc) * XC + ci_b] : f2bf(0.0f);
-        acc[tap] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[tap], 0, 0, 0);
+        for (int ta = 0; ta < 3; ++ta) xrow(py + ta, xf[(p + ta) % 3]);
       }
+      const bf16x8 a = *reinterpret_cast<const bf16x8*>(ga + py * (2 * TW));
+#pragma unroll
+      for (int tap = 0; tap < 9; ++tap)
+        acc[tap] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, xf[(p + tap / 3) % 3][tap % 3], acc[tap], 0, 0, 0);
+      if (nb == 0) accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ones, accb, 0, 0, 0);
     }
     __syncthreads();
   }
@@ -208,11 +290,12 @@ __global__ void __launch_bounds__(256) k_wgrad_mfma(const bf16* g, const bf16* x
   float* red = reinterpret_cast<float*>(lds);
   if (RG == 2 && rg == 1) {
 #pragma unroll
-    for (int tap = 0; tap < 9; ++tap)
+    for (int i = 0; i < 4; ++i) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) red[((pair * 9 + tap) * 4 + i) * 64 + lane] = acc[tap][i];
+      for (int tap = 0; tap < 9; ++tap) red[((pair * 10 + tap) * 4 + i) * 64 + lane] = acc[tap][i];
+      red[((pair * 10 + 9) * 4 + i) * 64 + lane] = accb[i];
+    }
   }
-  bred[tid] = accb;
   __syncthreads();
   float* out = partial + (size_t)blockIdx.x * (size_t)(gcr * xcr * 9 + gcr);
   if (rg == 0) {
@@ -220,29 +303,44 @@ __global__ void __launch_bounds__(256) k_wgrad_mfma(const bf16* g, const bf16* x
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int co = mb * 16 + 4 * kc + i;
-      if (co >= gcr || ci >= xcr) continue;
+      if (co >= gcr) continue;
+      if (ci < xcr) {
 #pragma unroll
-      for (int tap = 0; tap < 9; ++tap) {
-        float v = acc[tap][i];
-        if (RG == 2) v += red[((pair * 9 + tap) * 4 + i) * 64 + lane];
-        out[((size_t)co * xcr + ci) * 9 + tap] = v;
+        for (int tap = 0; tap < 9; ++tap) {
+          float v = acc[tap][i];
+          if (RG == 2) v += red[((pair * 10 + tap) * 4 + i) * 64 + lane];
+          out[((size_t)co * xcr + ci) * 9 + tap] = v;
+        }
+      }
+      if (nb == 0 && m == 0) {
+        float v = accb[i];
+        if (RG == 2) v += red[((pair * 10 + 9) * 4 + i) * 64 + lane];
+        out[(size_t)gcr * xcr * 9 + co] = v;
       }
     }
   }
-  if (tid < gcr) {
-    float sb = 0.0f;
-    for (int j = 0; j < 256 / GC; ++j) sb += bred[j * GC + tid];
-    out[(size_t)gcr * xcr * 9 + tid] = sb;
-  }
 }
 
-// grad[k] = sum over blocks (fixed order) of partial[b][k]
-__global__ void __launch_bounds__(256) k_reduce_partials(const float* partial, int nblocks, int len, float* grad) {
-  const int k = blockIdx.x * 256 + threadIdx.x;
-  if (k >= len) return;
+// grad[k] = sum over blocks (fixed order) of partial[b][k].  A block sums 32
+// columns, eight threads to a column (one thread per column left 37 blocks
+// with a chain of 256 loads each: 62 us a layer).
+constexpr int kRedCols = 32, kRedRows = 8;
+__global__ void __launch_bounds__(kRedCols * kRedRows) k_reduce_partials(const float* partial, int nblocks, int len,
+                                                                        float* grad) {
+  const int c = threadIdx.x % kRedCols, r = threadIdx.x / kRedCols;
+  const int k = blockIdx.x * kRedCols + c;
   double s = 0.0;
-  for (int b = 0; b < nblocks; ++b) s += partial[(size_t)b * len + k];
-  grad[k] = (float)s;
+  if (k < len) {
+#pragma unroll 8
+    for (int b = r; b < nblocks; b += kRedRows) s += partial[(size_t)b * len + k];
+  }
+  __shared__ double red[kRedRows][kRedCols];
+  red[r][c] = s;
+  __syncthreads();
+  if (r == 0 && k < len) {
+    for (int i = 1; i < kRedRows; ++i) s += red[i][c];
+    grad[k] = (float)s;
+  }
 }
 
 // Adam with bias correction (Kingma & Ba): fp32 master parameters.
@@ -445,7 +543,7 @@ hipError_t run_backward(ils_net* n, const float* t, int B, int H, int W) {
   hipLaunchKernelGGL(k_loss_grad, dim3(kLossBlocks), dim3(256), 0, st, n->zbuf, t, n->gbuf[0], n->lpart, B, H, W);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(64), 0, st, n->lpart, kLossBlocks, 3.0 * (double)px, n->loss);
+  hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kLossBlocks), 0, st, n->lpart, 3.0 * (double)px, n->loss);
   e = hipGetLastError();
   int cur = 0;
   for (int i = 5; i >= 0 && e == hipSuccess; --i) {
@@ -464,8 +562,8 @@ hipError_t run_backward(ils_net* n, const float* t, int B, int H, int W) {
                          B, H, W);
     e = hipGetLastError();
     if (e != hipSuccess) break;
-    hipLaunchKernelGGL(k_reduce_partials, dim3((len + 255) / 256), dim3(256), 0, st, n->partial, kWgradBlocks, len,
-                       n->grad + L.w_off);
+    hipLaunchKernelGGL(k_reduce_partials, dim3((len + kRedCols - 1) / kRedCols), dim3(kRedCols * kRedRows), 0, st,
+                       n->partial, kWgradBlocks, len, n->grad + L.w_off);
     e = hipGetLastError();
     if (e != hipSuccess || i == 0) break;
     ConvArgs a{};

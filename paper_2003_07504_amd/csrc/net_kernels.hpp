@@ -266,6 +266,20 @@ __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(M
           for (int i = 0; i < 3; ++i) fpix[r][nb][i] = in ? a.f[base + i * plane] : 0.0f;
         }
     }
+    // CONV_DGRAD: the activations behind the mask, likewise
+    uint2 mraw[2][2][MB];
+    if constexpr (MODE == CONV_DGRAD) {
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) {
+          const int y = imin(y0 + wave * 2 + r, H - 1), x = imin(x0 + nb * 16 + (lane & 15), W - 1);
+          const size_t pix = (size_t)img * plane + (size_t)y * W + x;
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb)
+            mraw[r][nb][mb] = *reinterpret_cast<const uint2*>(&a.mask[pix * COP + mb * 16 + 4 * (lane >> 4)]);
+        }
+    }
     f32x4 acc[2][2][MB];
     conv_mfma<CIP, COP, LW>(tile + cur * TILE, wf, wave * 2, acc);
     if (t + G < t_end) nx.store(tile + (cur ^ 1) * TILE);
@@ -289,8 +303,7 @@ __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(M
             for (int i = 0; i < 4; ++i) o[i] = f2bf(fmaxf(d[i] + bias[mb][i], 0.0f));
             *reinterpret_cast<uint2*>(&a.out[pix * COP + co0]) = *reinterpret_cast<const uint2*>(o);
           } else if constexpr (MODE == CONV_DGRAD) {
-            const uint2 mraw = *reinterpret_cast<const uint2*>(&a.mask[pix * COP + co0]);
-            const bf16* m = reinterpret_cast<const bf16*>(&mraw);
+            const bf16* m = reinterpret_cast<const bf16*>(&mraw[r][nb][mb]);
             bf16 o[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) o[i] = f2bf(bf2f(m[i]) > 0.0f ? d[i] : 0.0f);
