@@ -67,6 +67,20 @@ struct FrameDesc {
                     // kernel's full height need); see row_bands
 };
 
+// Work lists of smoothings of one plane with up to kMaxLevels lambdas, which
+// the kernel that makes the plane writes to the workspace header (as a batch's
+// are uploaded): levels first[g] .. first[g + 1] - 1 run as group g, their
+// descriptors from descs, the group's starts (row bands, then column tiles,
+// kMaxLevels + 1 of each) from starts + 2 g (kMaxLevels + 1).
+constexpr int kMaxLevels = 4;
+struct LevelLists {
+  FrameDesc d[kMaxLevels];
+  int ngroups, first[3];
+  int bands[2], tiles[2];  // per level of a group
+  FrameDesc* descs;
+  int* starts;
+};
+
 // Bands of the row passes.  A channel's H rows are split into nb bands, band
 // b holding rows [b H / nb, (b + 1) H / nb) (floor or ceil of H / nb rows);
 // nb is the frame's own count, kept within [ceil(H / G), H] so that no band
