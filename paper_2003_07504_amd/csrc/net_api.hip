@@ -482,11 +482,11 @@ int rec(ils_net* n, hipError_t e) {
 
 // Workgroups of `kernel` the current device holds at once (the convolution
 // kernels loop over tiles, so a larger grid only adds weight reloads).
-int resident_blocks(const void* kernel) {
+int resident_blocks(const void* kernel, int threads = NTHREADS) {
   int dev = 0, cus = 0, per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 1024;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 1024;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, NTHREADS, 0) != hipSuccess || per_cu <= 0)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu <= 0)
     per_cu = 1;
   return cus * per_cu;
 }
@@ -534,6 +534,43 @@ hipError_t run_forward(ils_net* n, const float* f, const float* lam, const float
     }
   }
   return e;
+}
+
+// The network without its hidden activations (inference): strips of SW
+// columns, each cut into segments down the image so that the chip's compute
+// units (one workgroup each) all have the same number of steps.  A segment of
+// r rows takes r / 2 + 12 steps (the rows its halo recomputes and the depth of
+// the pipeline), so more segments than it takes to fill the rounds cost time.
+// In place, where other strips' halos would be overwritten, layer by layer.
+hipError_t run_stream(ils_net* n, const float* f, const float* lam, const float* p, int B, int H, int W, float* v) {
+  const size_t vals = (size_t)B * 3 * H * W;
+  if (f < v + vals && v < f + vals) return run_forward(n, f, lam, p, B, H, W, v);
+  static const int cus = resident_blocks(reinterpret_cast<const void*>(&k_net_stream), 512);
+  StreamArgs a{};
+  a.f = f;
+  a.lam = lam;
+  a.p = p;
+  a.v = v;
+  for (int i = 0; i < 6; ++i) {
+    a.wfrag[i] = n->wf[i];
+    a.bias[i] = n->bias[i];
+  }
+  a.H = H;
+  a.W = W;
+  a.strips = (W + SW - 1) / SW;
+  const long long units = (long long)B * a.strips;
+  a.segs = 1;
+  long long best = -1;
+  for (int g = 1; g <= (H + 1) / 2 && (g == 1 || units * g <= 4LL * cus); ++g) {
+    const long long rounds = (units * g + cus - 1) / cus;
+    const long long cost = rounds * (((H + g - 1) / g + 1) / 2 + 12);
+    if (best < 0 || cost < best) {
+      best = cost;
+      a.segs = g;
+    }
+  }
+  hipLaunchKernelGGL(k_net_stream, dim3((unsigned)(units * a.segs)), dim3(512), 0, n->stream, a);
+  return hipGetLastError();
 }
 
 // gradients of the loss for the batch whose forward pass is in n->act / zbuf
@@ -665,7 +702,7 @@ int ils_net_forward(ils_net* n, const float* f, const float* lam, const float* p
   if (!n || !f || !lam || !p || !v) return ILS_ERR_INVALID_ARG;
   int rc = check_batch(n, B, H, W);
   if (rc != ILS_OK) return rc;
-  return rec(n, run_forward(n, f, lam, p, B, H, W, v));
+  return rec(n, run_stream(n, f, lam, p, B, H, W, v));
 }
 
 int ils_net_gradients(ils_net* n, const float* f, const float* lam, const float* p, const float* target, int B, int H,
@@ -723,7 +760,7 @@ static int surrogate_infer_bound(ils_net* n, ils_plan* plan, const float* f, con
                                  const float* lam_host, const float* p_host, float eps, int N, int B, int H, int W,
                                  float tau, float* out, float* tv_scratch, float* residual_host, int* fallback_host) {
   int rc = ILS_OK;
-  hipError_t e = run_forward(n, f, lam_dev, p_dev, B, H, W, out);
+  hipError_t e = run_stream(n, f, lam_dev, p_dev, B, H, W, out);
   if (e != hipSuccess) return rec(n, e);
   const size_t img = (size_t)3 * H * W;
   std::vector<const float*> pa(B), pb(B);
@@ -790,7 +827,7 @@ static int surrogate_infer_frames_bound(ils_net* n, ils_plan* plan, const ils_fr
     const ils_frame& fr = frames[i];
     hipLaunchKernelGGL(k_set_pair, dim3(1), dim3(64), 0, n->stream, lp, fr.lambda, fr.p);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = run_forward(n, fr.f, lp, lp + 1, 1, fr.H, fr.W, fr.out);
+    if (e == hipSuccess) e = run_stream(n, fr.f, lp, lp + 1, 1, fr.H, fr.W, fr.out);
     if (e != hipSuccess) return rec(n, e);
     const size_t img = (size_t)3 * fr.H * fr.W;
     tv[i] = ils_frame{fr.f, tv_scratch + off, fr.H, fr.W, 3, fr.lambda, fr.p, fr.eps, 1, fr.out,

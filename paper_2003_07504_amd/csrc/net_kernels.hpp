@@ -332,4 +332,254 @@ __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(M
   }
 }
 
+// ------------------------------------------------ whole network, one launch
+// Inference needs no hidden activation afterwards, and layer by layer each
+// one moves 64 bytes per pixel out to HBM and back (213 us a 32 -> 32 layer
+// for 8 frames of 1280 x 720, 88 % of the rate of a plain copy, the matrix
+// cores at a quarter of theirs).  Here a workgroup streams a strip of the
+// image from top to bottom and keeps the last rows of every layer in LDS:
+//   * a strip yields SW = 54 output columns from 64 columns of work per layer
+//     (layer l needs 6 - l columns more on either side; layer 1 uses all 64);
+//   * in a step every layer makes two rows, each layer one step and one row
+//     pair behind the layer before it: layer l makes row pair k (rows
+//     ya - (6 - l) + 2 k and the next one, ya the first output row) in step
+//     k + 2 l, from pairs k and k + 1 of layer l - 1; six rows (three pairs)
+//     of each layer are held, the pair being written among them.  Layer 0 is
+//     the packed input.  One barrier per step;
+//   * the eight waves keep their layer's weights in registers: waves 2 i and
+//     2 i + 1 do layer 2 + i on 32 columns each; the first four also do a 16
+//     column block of the last layer, the other four one of the first, so
+//     that the waves of a SIMD (i and i + 4) have 174 products per step in
+//     all;
+//   * two rows per step because the operand read from LDS (1 KB for every two
+//     products) then serves three: at one row per step the LDS would be as
+//     busy as the matrix cores.
+// A product sums in the order of k_conv, so the results are the same bits.
+// 8 frames of 1280 x 720: 1222 -> 650 us (1.4 PFLOP/s of products, padding
+// and halos included); one 256 x 256 crop 70 -> 55.
+constexpr int SW = 54, SPX = 66, SROWS = 6;  // output columns, columns and rows held per layer
+constexpr int SROWB = SPX * 64;              // bytes of a 32-channel row
+constexpr int SLAYERB = SROWS * SROWB;
+constexpr int SIN_ROWB = SPX * 16;           // bytes of a row of the packed input
+constexpr int STREAM_LDS = 5 * SLAYERB + SROWS * SIN_ROWB;
+
+struct StreamArgs {
+  const float* f;        // planar fp32 input images (B, 3, H, W)
+  const float* lam;      // B
+  const float* p;        // B
+  float* v;              // planar fp32 output
+  const bf16* wfrag[6];
+  const float* bias[6];
+  int H, W, strips, segs;  // strips across, segments down an image
+};
+
+// Byte offset of channels 8 chunk .. 8 chunk + 7 of pixel px in a 32-channel
+// row.  The 16-byte chunks of a pixel are permuted by px / 4, so that 16
+// consecutive pixels' chunks cover all banks.
+__device__ __forceinline__ int stream_off(int px, int chunk) { return px * 64 + ((chunk ^ ((px >> 2) & 3)) << 4); }
+
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) k_net_stream(StreamArgs a) {
+  __shared__ __attribute__((aligned(16))) unsigned char lds[STREAM_LDS];
+  unsigned char* xin = lds + 5 * SLAYERB;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int seg = blockIdx.x % a.segs, rest = blockIdx.x / a.segs;
+  const int strip = rest % a.strips, img = rest / a.strips;
+  const int H = a.H, W = a.W;
+  const int ya = (int)((long long)seg * H / a.segs), yb = (int)((long long)(seg + 1) * H / a.segs);
+  const int xs = strip * SW;
+  const size_t plane = (size_t)H * W;
+  const float* f = a.f + (size_t)img * 3 * plane;
+  float* v = a.v + (size_t)img * 3 * plane;
+  const int n6 = (yb - ya + 1) / 2;  // row pairs of the output
+
+  const int layer = 2 + (wave >> 1), half = wave & 1;
+  const int q = wave & 3;          // this wave's 16-column block of the first or last layer
+  const bool last = wave < 4;      // ... of the last one
+  bf16x8 wf[2][9], ex[9];
+  load_wfrag<32, 32>(a.wfrag[layer - 1], wf);
+  float bias[2][4], exb[2][4];
+#pragma unroll
+  for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bias[mb][i] = a.bias[layer - 1][mb * 16 + 4 * (lane >> 4) + i];
+  if (last) {
+    bf16x8 w[1][9];
+    load_wfrag<32, 16>(a.wfrag[5], w);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) ex[k] = w[0][k];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) exb[0][i] = a.bias[5][4 * (lane >> 4) + i], exb[1][i] = 0.0f;
+  } else {
+    bf16x8 w[2][3];
+    load_wfrag<8, 32>(a.wfrag[0], w);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) ex[k] = k < 6 ? w[k / 3][k % 3] : w[0][0];
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) exb[mb][i] = a.bias[0][mb * 16 + 4 * (lane >> 4) + i];
+  }
+
+  // per-lane read offsets of a 16-column block at column 0, tap column tc
+  int rd[3];
+#pragma unroll
+  for (int tc = 0; tc < 3; ++tc) rd[tc] = stream_off((lane & 15) + tc, lane >> 4);
+  // four channels (one accumulator) of pixel lane & 15: chunk 2 mb + lane / 32, its half (lane / 16) & 1
+  int wr[2];
+#pragma unroll
+  for (int mb = 0; mb < 2; ++mb) wr[mb] = stream_off(lane & 15, 2 * mb + (lane >> 5)) + ((lane >> 4) & 1) * 8;
+
+  // packed input: thread t < 2 SPX takes pixel (t / SPX, t % SPX) of a row pair
+  const bool loads = tid < 2 * SPX;
+  const int irow = tid >= SPX ? 1 : 0, ipx = tid - irow * SPX;
+  const int gx = loads ? wrapi(xs - 6 + ipx, W) : 0;
+  const bf16 lam = f2bf(a.lam[img]), pp = f2bf(a.p[img]);
+  float in[3];
+  auto fetch = [&](int k) {
+    if (!loads) return;
+    const float* src = f + (size_t)wrapi(ya - 6 + 2 * k + irow, H) * W + gx;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) in[c] = src[c * plane];
+  };
+  fetch(0);
+
+  auto relu4 = [&](const f32x4& d, const float (&b)[4], unsigned char* dst) {
+    bf16 o[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = f2bf(fmaxf(d[i] + b[i], 0.0f));
+    *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(o);
+  };
+
+  const int steps = n6 + 12;
+  int slot = 0;  // s mod 3
+  for (int s = 0; s < steps; ++s) {
+    if (loads && s < n6 + 6) {  // layer 0: pair s, loaded in the step before
+      bf16 o[8];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) o[c] = f2bf(in[c]);
+      o[3] = lam;
+      o[4] = pp;
+      o[5] = o[6] = o[7] = f2bf(0.0f);
+      *reinterpret_cast<uint4*>(xin + (2 * slot + irow) * SIN_ROWB + ipx * 16) = *reinterpret_cast<const uint4*>(o);
+      if (s + 1 < n6 + 6) fetch(s + 1);
+    }
+    // pair k of any layer sits in slot k mod 3 of its rows
+    // ---- layer `layer`, columns 32 half .. + 31
+    auto hidden = [&]() __attribute__((always_inline)) {
+      const int k = s - 2 * layer;
+      if (k >= 0 && k < n6 + 6 - layer) {
+        const unsigned char* src = lds + (layer - 2) * SLAYERB + half * 2048;
+        // pairs k and k + 1 of layer - 1: slots of k and k + 1
+        const int s0 = k % 3, s1 = (k + 1) % 3;
+        f32x4 acc[2][2][2];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i >> 2][(i >> 1) & 1][i & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const unsigned char* row = src + ((r < 2 ? s0 : s1) * 2 + (r & 1)) * SROWB;
+#pragma unroll
+          for (int tc = 0; tc < 3; ++tc)
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) {
+              const bf16x8 b = *reinterpret_cast<const bf16x8*>(row + rd[tc] + nb * 1024);
+#pragma unroll
+              for (int o = 0; o < 2; ++o) {
+                const int ta = r - o;
+                if (ta < 0 || ta > 2) continue;
+#pragma unroll
+                for (int mb = 0; mb < 2; ++mb)
+                  acc[o][nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[mb][ta * 3 + tc], b, acc[o][nb][mb], 0, 0, 0);
+              }
+            }
+        }
+        unsigned char* dst = lds + (layer - 1) * SLAYERB + s0 * 2 * SROWB + half * 2048;
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+          for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) relu4(acc[o][nb][mb], bias[mb], dst + o * SROWB + nb * 1024 + wr[mb]);
+      }
+    };
+    // Waves 0 .. 3 do their hidden layer first, the others last, so that the two
+    // waves of a SIMD are not in the same phase of a step (658 -> 649 us for 8
+    // frames of 1280 x 720).
+    if (last) {
+      hidden();
+      // ---- last layer, columns 16 q .. + 15: v = f + z
+      const int k = s - 12;
+      if (k >= 0) {
+        const int x = xs + q * 16 + (lane & 15);
+        const bool col = lane < 16 && q * 16 + lane < SW && x < W;
+        float fv[2][3];
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+          const int y = ya + 2 * k + o;
+          const size_t at = col && y < yb ? (size_t)y * W + x : 0;
+#pragma unroll
+          for (int c = 0; c < 3; ++c) fv[o][c] = f[at + c * plane];
+        }
+        const unsigned char* src = lds + 4 * SLAYERB + q * 1024;
+        const int s0 = k % 3, s1 = (k + 1) % 3;
+        f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const unsigned char* row = src + ((r < 2 ? s0 : s1) * 2 + (r & 1)) * SROWB;
+#pragma unroll
+          for (int tc = 0; tc < 3; ++tc) {
+            const bf16x8 b = *reinterpret_cast<const bf16x8*>(row + rd[tc]);
+#pragma unroll
+            for (int o = 0; o < 2; ++o) {
+              const int ta = r - o;
+              if (ta < 0 || ta > 2) continue;
+              acc[o] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ex[ta * 3 + tc], b, acc[o], 0, 0, 0);
+            }
+          }
+        }
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+          const int y = ya + 2 * k + o;
+          if (col && y < yb) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[(size_t)y * W + x + c * plane] = fv[o][c] + acc[o][c] + exb[0][c];
+          }
+        }
+      }
+    } else {
+      // ---- first layer, columns 16 q .. + 15: a K block is four taps of eight channels
+      const int k = s - 2;
+      if (k >= 0 && k < n6 + 5) {
+        const int s0 = k % 3, s1 = (k + 1) % 3;
+        f32x4 acc[2][2];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kb = 0; kb < 3; ++kb) {
+          int tap = kb * 4 + (lane >> 4);
+          if (tap > 8) tap = 8;  // zero weights there
+          const int ta = tap / 3, tc = tap - 3 * ta;
+#pragma unroll
+          for (int o = 0; o < 2; ++o) {
+            const int r = o + ta;
+            const bf16x8 b = *reinterpret_cast<const bf16x8*>(xin + ((r < 2 ? s0 : s1) * 2 + (r & 1)) * SIN_ROWB +
+                                                              (q * 16 + (lane & 15) + tc) * 16);
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb)
+              acc[o][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ex[mb * 3 + kb], b, acc[o][mb], 0, 0, 0);
+          }
+        }
+        unsigned char* dst = lds + s0 * 2 * SROWB + q * 1024;
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+          for (int mb = 0; mb < 2; ++mb) relu4(acc[o][mb], exb[mb], dst + o * SROWB + wr[mb]);
+      }
+      hidden();
+    }
+    slot = slot == 2 ? 0 : slot + 1;
+    __syncthreads();
+  }
+}
+
 }  // namespace ilsn
