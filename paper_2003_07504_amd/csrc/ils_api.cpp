@@ -99,7 +99,7 @@ constexpr size_t kGraphCache = 4;  // batch graphs kept per plan
 
 // Per-length device tables (offsets into the plan's table buffer).
 struct LenTables {
-  size_t tw, tw2, sx, sy, twm;  // byte offsets
+  size_t tw, tw2, sx, sy, twm, twc;  // byte offsets
 };
 
 // Pinned host staging for the small host-to-device uploads (batch work
@@ -278,7 +278,7 @@ static void fill_desc_on(const char* tables, const std::map<int, LenTables>& tab
   d.twm_row = reinterpret_cast<const cf*>(tables + tr.twm);
   d.sx = reinterpret_cast<const float*>(tables + tr.sx);
   d.tw_col = reinterpret_cast<const cf*>(tables + tc.tw);
-  d.twm_col = reinterpret_cast<const cf*>(tables + tc.twm);
+  d.twm_col = reinterpret_cast<const cf*>(tables + tc.twc);
   d.sy = reinterpret_cast<const float*>(tables + tc.sy);
   d.H = H;
   d.W = W;
@@ -333,6 +333,11 @@ struct HostTables {
       // rows of Q|1 entries, entry [k1][t] = exp(-2 pi i t k1 / L): lanes
       // that walk either index hit distinct banks
       if (o) t.twm = put(sizeof(cf) * o->P * (o->Q | 1));
+      // the column pass's: the same, or W_L^(k1 j) and W_(r2 r3)^(k2 n3) of
+      // the three-stage split
+      t.twc = t.twm;
+      const int r1 = o ? o->c3.r1 : 0, r2 = o ? o->c3.r2 : 0, r3 = o ? o->c3.r3 : 0;
+      if (r1) t.twc = put(sizeof(cf) * (L + r2 * r3));
       cf* tw = reinterpret_cast<cf*>(host.data() + t.tw);
       cf* tw2 = reinterpret_cast<cf*>(host.data() + t.tw2);
       float* sx = reinterpret_cast<float*>(host.data() + t.sx);
@@ -357,6 +362,13 @@ struct HostTables {
         const int Q = o->Q, QP = Q | 1;
         for (int k1 = 0; k1 < o->P; ++k1)
           for (int q = 0; q < QP; ++q) twm[k1 * QP + q] = q < Q ? tw[q * k1] : cf{0.0f, 0.0f};
+      }
+      if (r1) {
+        cf* c = reinterpret_cast<cf*>(host.data() + t.twc);
+        for (int k = 0; k < r1; ++k)
+          for (int j = 0; j < r2 * r3; ++j) *c++ = tw[k * j];
+        for (int k = 0; k < r2; ++k)
+          for (int j = 0; j < r3; ++j) *c++ = tw[r1 * k * j];
       }
       tab[L] = t;
     }
@@ -518,17 +530,12 @@ static Pick rule_pick(const FrameDesc& d, int cus) {
   for (int i = 1; i < orow->nrow; ++i)
     if (orow->row[i].rows[ilsk::ROW_MID] > pk.rv->rows[ilsk::ROW_MID]) pk.rv = &orow->row[i];
   if (cus <= 0) return pk;
-  const ColVariant* narrow = pk.cv;
-  bool found = false;
-  for (int i = 0; i < ocol->ncol_all; ++i) {
-    const ColVariant* v = &ocol->col[i];
-    if (v->cols < narrow->cols) narrow = v;
-    if (10LL * col_items(v, d) >= 7LL * cus && (!found || v->cols > pk.cv->cols)) {
-      pk.cv = v;
-      found = true;
-    }
+  // (a three-stage length's tiles beyond the two of 8 and 4 are the tuner's)
+  const int n = ocol->c3.r1 ? 2 : ocol->ncol_all;
+  for (int i = 0; i < n; ++i) {
+    pk.cv = &ocol->col[i];
+    if (10LL * col_items(pk.cv, d) >= 7LL * cus) break;
   }
-  if (!found) pk.cv = narrow;
   return pk;
 }
 

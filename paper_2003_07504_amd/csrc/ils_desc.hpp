@@ -48,6 +48,7 @@ struct FrameDesc {
   const float* sx;    // 4 sin^2(pi k / W), k <= M
   const cf* tw_col;   // exp(-2 pi i j / H), j < H
   const cf* twm_col;  // exp(-2 pi i j k1 / H) at [k1 * (Q|1) + j], H = P Q
+                      // (three stages: see col3_body)
   const float* sy;    // 4 sin^2(pi l / H), l < H
   int H, W, C, ldS;
   float kappa;      // lambda * c / 2, c >= c0 = p eps^(p/2 - 1) (Welsch: c = 2)

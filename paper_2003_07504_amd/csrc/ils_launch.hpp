@@ -105,6 +105,17 @@ __attribute__((amdgpu_waves_per_eu(ColCfg<P, Q, S>::WAVES))) k_col(WorkList wl) 
   col_body<P, Q, S>(d, local - ch * nb, ch, smem);
 }
 
+// The same for the three-stage column pass (at most 128 VGPRs per lane).
+template <int H, int S>
+__global__ void __launch_bounds__((Col3Geom<H, S>::THREADS)) __attribute__((amdgpu_waves_per_eu(4))) k_col3(WorkList wl) {
+  __shared__ float smem[Col3Geom<H, S>::LDS_F];
+  int local;
+  const FrameDesc d = resolve(wl, blockIdx.x, local);
+  const int nb = col_tiles(d, S);
+  const int ch = local / nb;
+  col3_body<H, S>(d, local - ch * nb, ch, smem);
+}
+
 // Host-side table of one length's launchers (one block per work item).  Of
 // its row-band and column-tile shapes the plan's tuner times the first nrow
 // and ncol; the column tiles up to ncol_all are for the rule that serves
@@ -123,6 +134,7 @@ constexpr int kMaxShapes = 6;
 struct LenOps {
   int L, P, Q;
   int nrow, ncol, ncol_all;
+  Split3 c3;  // split of the three-stage column pass (r1 = 0: two stages)
   RowVariant row[kMaxShapes];
   ColVariant col[kMaxShapes];
 };
@@ -161,6 +173,12 @@ RowVariant row_variant() {
   using C = RowCfg<P, Q, G>;
   return RowVariant{{G, G, C::GF}, C::THREADS, 4 * C::LDS_F, &launch_row<P, Q, G>};
 }
+template <int H, int S>
+hipError_t launch_col3(const WorkList& wl, hipStream_t st) {
+  hipLaunchKernelGGL((k_col3<H, S>), dim3(wl.total), dim3(Col3Geom<H, S>::THREADS), 0, st, wl);
+  return hipGetLastError();
+}
+
 template <int P, int Q, int S>
 ColVariant col_variant() {
   using C = ColCfg<P, Q, S>;
@@ -179,6 +197,14 @@ void add_col(LenOps& o) {
     if (o.col[i].cols == S) return;
   o.col[o.ncol_all++] = col_variant<P, Q, S>();
 }
+// Three-stage tiles in order of preference: 8 columns (half lines), 4 for
+// few blocks; 12 and 2 columns are for the tuner to try.
+template <int H, int S>
+void add_col3(LenOps& o) {
+  if constexpr (Col3Geom<H, S>::THREADS <= 1024)
+    o.col[o.ncol_all++] = ColVariant{S, Col3Geom<H, S>::THREADS, 4 * Col3Geom<H, S>::LDS_F, &launch_col3<H, S>};
+}
+
 template <int P, int Q>
 LenOps start_ops(int L) {
   LenOps o{};
@@ -188,28 +214,45 @@ LenOps start_ops(int L) {
   return o;
 }
 
-// Timed alternatives are compiled only for lengths where they can matter;
-// shorter columns get narrower tiles for the rule.  Entry 0 is the default
-// shape (used when the tuner is off or cannot time).
+// The column tiles of a length; timed ones (ncol) for tuned lengths of 480
+// and more, else entry 0 and narrower tiles for the rule.
+template <int P, int Q>
+void add_cols(LenOps& o, bool tuned) {
+  if constexpr (col3_length(P * Q)) {
+    o.c3 = split3(P * Q);
+    add_col3<P * Q, 8>(o);
+    add_col3<P * Q, 4>(o);
+    o.ncol = tuned ? o.ncol_all : 1;
+  } else {
+    add_col<P, Q, col_tile<P, Q>()>(o);
+    o.ncol = 1;
+    if constexpr (P * Q >= 480) {
+      if (tuned) add_col<P, Q, col_tile_alt<P, Q, 0>()>(o);
+    }
+    add_col<P, Q, col_tile_alt<P, Q, 1>()>(o);
+    add_col<P, Q, col_tile_alt<P, Q, 2>()>(o);
+    if (tuned && P * Q >= 480) o.ncol = o.ncol_all;
+  }
+}
+
+// Timed alternatives are compiled only for lengths where they can matter.
+// Entry 0 is the default shape (used when the tuner is off or cannot time).
 template <int P, int Q>
 LenOps make_ops(int L) {
   LenOps o = start_ops<P, Q>(L);
   add_row<P, Q, row_band<P, Q>()>(o);
-  add_col<P, Q, col_tile<P, Q>()>(o);
+  add_cols<P, Q>(o, true);
   if constexpr (P * Q >= 480) {
     add_row<P, Q, row_band_alt<P, Q, 0>()>(o);
     add_row<P, Q, row_band_alt<P, Q, 1>()>(o);
     add_row<P, Q, row_band_alt<P, Q, 2>()>(o);
     add_row<P, Q, row_band_alt<P, Q, 3>()>(o);
     add_row<P, Q, row_band_alt<P, Q, 4>()>(o);
-    add_col<P, Q, col_tile_alt<P, Q, 0>()>(o);
-    add_col<P, Q, col_tile_alt<P, Q, 1>()>(o);
-    add_col<P, Q, col_tile_alt<P, Q, 2>()>(o);
-    o.ncol = o.ncol_all;
-  } else {
-    o.ncol = o.ncol_all;
-    add_col<P, Q, col_tile_alt<P, Q, 1>()>(o);
-    add_col<P, Q, col_tile_alt<P, Q, 2>()>(o);
+    if constexpr (col3_length(P * Q)) {
+      add_col3<P * Q, 12>(o);
+      add_col3<P * Q, 2>(o);
+      o.ncol = o.ncol_all;
+    }
   }
   return o;
 }
@@ -219,10 +262,7 @@ template <int P, int Q>
 LenOps make_more_ops(int L) {
   LenOps o = start_ops<P, Q>(L);
   add_row<P, Q, row_band_wide<P, Q>()>(o);
-  add_col<P, Q, col_tile<P, Q>()>(o);
-  o.ncol = o.ncol_all;
-  add_col<P, Q, col_tile_alt<P, Q, 1>()>(o);
-  add_col<P, Q, col_tile_alt<P, Q, 2>()>(o);
+  add_cols<P, Q>(o, false);
   return o;
 }
 

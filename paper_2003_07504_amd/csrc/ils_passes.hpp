@@ -25,8 +25,7 @@
 
 namespace ilsk {
 
-__device__ __forceinline__ int imax(int a, int b) { return a > b ? a : b; }
-__device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
+constexpr int imax_c(int a, int b) { return a > b ? a : b; }
 
 // Normalised half-quadratic variable  mu / c = g (1 - (c0/c) (1 + g^2/eps)^(p/2 - 1))
 // (Eq. (7) divided by c, c0 = p eps^(p/2-1)), for a difference h = g / sqrt(eps)
@@ -752,6 +751,162 @@ __device__ __forceinline__ void col_body(const FrameDesc& d, int tile, int ch, f
       static_for<P>([&](auto n1c) {
         constexpr int n1 = decltype(n1c)::value;
         put<(S_ >= 12)>(out + (size_t)(Q * n1) * ldS, off, x[n1]);
+      });
+    }
+  }
+}
+
+// --------------------------------------------------------------------------
+// Column pass of lengths 400 .. 1000 in three stages, H = R1 R2 R3 with
+// factors of at most 16: a lane holds a third to a half of the two-stage
+// pass's values, so that the chain of instructions a single tile waits for
+// is short.  Frames of up to a few blocks per CU gain (480p RGB 6.5 -> 5.3
+// us, 720p grey 7.5 -> 6.1, RGB 9.9 -> 8.8), full chips stay as they are
+// (12 x 720p 24.2 -> 24.1); longer columns lose it again to the narrower
+// tiles (1080p RGB 16.4 -> 17.2), shorter ones to the extra exchange (96 x
+// 256 x 256: 10 -> 14).
+//   n = n1 R2 R3 + n2 R3 + n3,  k = k1 + R1 k2 + R1 R2 k3:
+// stage 1 over n1 (lane (n2, n3)), twiddle W_H^(k1 (n2 R3 + n3)); stage 2
+// over n2 (lane (k1, n3)), twiddle W_(R2 R3)^(k2 n3); stage 3 over n3 (lane
+// (k1, k2)), divide, and the same backwards.  Stages 2 and 3 exchange in
+// place: a lane rewrites the values it read.
+// --------------------------------------------------------------------------
+struct Split3 {
+  int r1, r2, r3;
+};
+// The split whose smallest factor is largest (fewest lanes), then whose
+// largest is smallest; an odd factor last (its rows of the exchange then need
+// no padding against bank conflicts).
+constexpr Split3 split3(int H) {
+  Split3 best{0, 0, 0};
+  int least = 1, most = 17;
+  for (int a = 16; a >= 2; --a)
+    for (int b = a; b >= 2; --b) {
+      if (H % (a * b) != 0) continue;
+      const int c = H / (a * b);
+      if (c > b || c < least || (c == least && a >= most)) continue;
+      least = c;
+      most = a;
+      best = c % 2 ? Split3{a, b, c} : b % 2 ? Split3{a, c, b} : a % 2 ? Split3{b, c, a} : Split3{a, b, c};
+    }
+  return best;
+}
+constexpr bool col3_length(int H) {
+  if (H < 400 || H > 1000) return false;
+  const Split3 s = split3(H);
+  const int least = s.r1 < s.r2 ? (s.r1 < s.r3 ? s.r1 : s.r3) : (s.r2 < s.r3 ? s.r2 : s.r3);
+  return s.r1 > 0 && 8 * (H / least) <= 1024;  // eight columns of the stage with the most lanes
+}
+
+template <int H, int S>
+struct Col3Geom {
+  static constexpr int R1 = split3(H).r1, R2 = split3(H).r2, R3 = split3(H).r3;
+  static constexpr int B1 = R2 * R3, B2 = R1 * R3, B3 = R1 * R2;  // lanes of the stages
+  static constexpr int T = imax_c(B1, imax_c(B2, B3));
+  static constexpr int R3P = R3 | 1;
+  static constexpr int THREADS = T * S;
+  static constexpr int LDS_F = 2 * R1 * R2 * R3P * S;
+};
+
+template <int H, int S>
+__device__ __forceinline__ void col3_body(const FrameDesc& d, int tile, int ch, float* smem) {
+  using G = Col3Geom<H, S>;
+  constexpr int R1 = G::R1, R2 = G::R2, R3 = G::R3;
+  cf* ex = reinterpret_cast<cf*>(smem);
+  const int ldS = d.ldS;
+  const int s = threadIdx.x % S, j = threadIdx.x / S;
+  const int bin = spec_bin(tile * S + s, d.W / 2, ldS);
+  const bool col_ok = bin >= 0;
+  const int cc = col_ok ? tile * S + s : 0;
+  const ILS_G cf* in = gm(d.specA) + (size_t)ch * H * ldS;
+  ILS_G cf* out = gm(d.specB) + (size_t)ch * H * ldS;
+  const unsigned off = 8u * (unsigned)(j * ldS + cc);
+  const ILS_G cf* g1 = gm(d.twm_col);       // W_H^(k1 j) at [k1 B1 + j]
+  const ILS_G cf* g2 = g1 + R1 * G::B1;     // W_(R2 R3)^(k2 n3) at [k2 R3 + n3]
+  auto at3 = [&](int k1, int m2, int n3) -> cf& { return ex[((k1 * R2 + m2) * G::R3P + n3) * S + s]; };
+  const int q3 = j / R3, m3 = j - q3 * R3;  // (n2, n3) in stage 1, (k1, n3) in stage 2
+  const int q2 = j / R2, m2 = j - q2 * R2;  // (k1, k2) in stage 3
+  cf w1[R1], w2[R2];
+  if (j < G::B1) {
+    cf x[R1];
+    static_for<R1>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      x[i] = col_ok ? cf(at<cf>(in + (size_t)(G::B1 * i) * ldS, off)) : cf{0.0f, 0.0f};
+    });
+    static_for<R1>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      if constexpr (i > 0) w1[i] = cf(g1[i * G::B1 + j]);
+    });
+    dft<R1, -1>(x);
+    static_for<R1>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      at3(i, q3, m3) = i == 0 ? x[i] : cmul(x[i], w1[i]);
+    });
+  }
+  __syncthreads();
+  if (j < G::B2) {
+    cf x[R2];
+    static_for<R2>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      x[i] = at3(q3, i, m3);
+      if constexpr (i > 0) w2[i] = cf(g2[i * R3 + m3]);
+    });
+    dft<R2, -1>(x);
+    static_for<R2>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      at3(q3, i, m3) = i == 0 ? x[i] : cmul(x[i], w2[i]);
+    });
+  }
+  __syncthreads();
+  if (j < G::B3) {
+    cf x[R3];
+    float sy[R3];
+    const ILS_G float* gsy = gm(d.sy) + (q2 + R1 * m2);
+    static_for<R3>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      sy[i] = gsy[R1 * R2 * i];
+      x[i] = at3(q2, m2, i);
+    });
+    const float kappa = d.kappa, scale = d.col_scale;
+    const float ksx = fmaf(kappa, gm(d.sx)[col_ok ? bin : 0], 1.0f);
+    dft<R3, -1>(x);
+    static_for<R3>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      x[i] = cscale(x[i], scale * __builtin_amdgcn_rcpf(fmaf(kappa, sy[i], ksx)));
+    });
+    dft<R3, +1>(x);
+    static_for<R3>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      at3(q2, m2, i) = x[i];
+    });
+  }
+  __syncthreads();
+  if (j < G::B2) {
+    cf x[R2];
+    static_for<R2>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      x[i] = at3(q3, i, m3);
+      if constexpr (i > 0) x[i] = cmulc(x[i], w2[i]);
+    });
+    dft<R2, +1>(x);
+    static_for<R2>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      at3(q3, i, m3) = x[i];
+    });
+  }
+  __syncthreads();
+  if (j < G::B1) {
+    cf x[R1];
+    static_for<R1>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      x[i] = at3(i, q3, m3);
+      if constexpr (i > 0) x[i] = cmulc(x[i], w1[i]);
+    });
+    dft<R1, +1>(x);
+    if (col_ok) {
+      static_for<R1>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        put<(S >= 12)>(out + (size_t)(G::B1 * i) * ldS, off, x[i]);
       });
     }
   }
