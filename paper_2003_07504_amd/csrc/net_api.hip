@@ -582,6 +582,9 @@ hipError_t run_backward(ils_net* n, const float* t, int B, int H, int W) {
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kLossBlocks), 0, st, n->lpart, 3.0 * (double)px, n->loss);
   e = hipGetLastError();
+  // no more blocks (partial rows to write and to sum) than there are tiles
+  const long long tiles = (long long)B * ((H + TH - 1) / TH) * ((W + TW - 1) / TW);
+  const int nblk = (int)(tiles < kWgradBlocks ? tiles : kWgradBlocks);
   int cur = 0;
   for (int i = 5; i >= 0 && e == hipSuccess; --i) {
     const Layer& L = kNet.L[i];
@@ -589,18 +592,18 @@ hipError_t run_backward(ils_net* n, const float* t, int B, int H, int W) {
     const bf16* x = n->act[i];
     const int len = L.co * L.ci * 9 + L.co;
     if (i == 5)
-      hipLaunchKernelGGL((k_wgrad_mfma<8, 32>), dim3(kWgradBlocks), dim3(256), 0, st, g, x, n->partial, L.co, L.ci, B,
+      hipLaunchKernelGGL((k_wgrad_mfma<8, 32>), dim3(nblk), dim3(256), 0, st, g, x, n->partial, L.co, L.ci, B,
                          H, W);
     else if (i == 0)
-      hipLaunchKernelGGL((k_wgrad_mfma<32, 8>), dim3(kWgradBlocks), dim3(256), 0, st, g, x, n->partial, L.co, L.ci, B,
+      hipLaunchKernelGGL((k_wgrad_mfma<32, 8>), dim3(nblk), dim3(256), 0, st, g, x, n->partial, L.co, L.ci, B,
                          H, W);
     else
-      hipLaunchKernelGGL((k_wgrad_mfma<32, 32>), dim3(kWgradBlocks), dim3(256), 0, st, g, x, n->partial, L.co, L.ci,
+      hipLaunchKernelGGL((k_wgrad_mfma<32, 32>), dim3(nblk), dim3(256), 0, st, g, x, n->partial, L.co, L.ci,
                          B, H, W);
     e = hipGetLastError();
     if (e != hipSuccess) break;
     hipLaunchKernelGGL(k_reduce_partials, dim3((len + kRedCols - 1) / kRedCols), dim3(kRedCols * kRedRows), 0, st,
-                       n->partial, kWgradBlocks, len, n->grad + L.w_off);
+                       n->partial, nblk, len, n->grad + L.w_off);
     e = hipGetLastError();
     if (e != hipSuccess || i == 0) break;
     ConvArgs a{};
