@@ -128,7 +128,7 @@ __global__ void __launch_bounds__(kLossBlocks) k_loss_final(const double* partia
   if (threadIdx.x == 0) *loss = (float)(red[0] / n);
 }
 
-// Partial weight and bias gradients of one convolution on the MFMA units:
+// Partial weight and bias gradients of a convolution on the MFMA units:
 //   dW[co][ci][tap] = sum_pixels g[pixel][co] x[pixel + shift(tap)][ci]
 // is, for each tap, D[co][ci] += sum_k G[co][k] X_tap[k][ci] with k running
 // over the 32 pixels of one tile row (one K block of v_mfma_f32_16x16x32_bf16).
@@ -144,18 +144,36 @@ __global__ void __launch_bounds__(kLossBlocks) k_loss_final(const double* partia
 // them round in registers and writes them to LDS channel by channel; a
 // fragment is then one 16-byte read, the tap one column on is the same ten
 // pixels shifted by 16 bits, and a row of x serves three rows of taps.  The
-// next tile's loads are in flight during a tile's products.  Reading
-// fragments element by element from NHWC tiles took 110 us a layer for 16
-// crops of 256 x 256 (134 MB); this takes
-// 42 us with two blocks per CU, 51 with one.
-template <int C, int ROWS, int QUADS, int ROWB>
+// next tile's loads are in flight during a tile's products.  (Fragments read
+// element by element from NHWC tiles took 110 us a 32-channel layer for 16
+// crops of 256 x 256.)
+//
+// PixTile: in LDS a row of a block of MW channels is one MW x 16 byte piece
+// per eight pixels, channel c of piece k in place c ^ k.  A 16-byte LDS read
+// serves sixteen lanes together that are not consecutive (0-3, 12-15, 20-27
+// and so on): with lane l reading channel l % 16 of piece l / 16, these have
+// sixteen places of their own, as have the 8-byte stores of 32 lanes.
+template <int C, int ROWS, int QUADS, bool PIXELS = false>
 struct PixTile {  // ROWS x 4 QUADS pixels of C channels, held channel-major in LDS
   static constexpr int CG = C / 8;                        // channel groups of 8
   static constexpr int ITEMS = ROWS * QUADS * CG;         // (row, 4 pixels, 8 channels)
   static constexpr int NIT = (ITEMS + 255) / 256;         // items per thread
-  static constexpr int CS = (ROWS * ROWB / 16 | 1) * 16;  // channel stride: an odd number of 16-byte units
-  static constexpr int BYTES = C * CS;
-  u32x4 v[NIT][4];
+  static constexpr int MW = C < 16 ? C : 16;              // channels of a block
+  static constexpr int RP = (QUADS + 1) / 2 * MW * 16;    // bytes of a block's row
+  static constexpr int BS = ROWS * RP + 64;               // bytes from one block to the next
+  static constexpr int BYTES = (C / MW - 1) * BS + ROWS * RP;
+  u32x4 v[NIT][4];  // v[j][p] is pixel p ^ turn() of item j
+
+  // Byte offset, within its row, of pixels 8 k .. 8 k + 7 of channel c.
+  __device__ __forceinline__ static int at(int c, int k) {
+    return c / MW * BS + k * (MW * 16) + (((c % MW) ^ k) % MW << 4);
+  }
+  // The order of an item's pixels: lanes that store together take different
+  // ones, or store_pixels() would send them to the same banks.
+  __device__ __forceinline__ static int turn(int i) {
+    const int q = i / CG;
+    return !PIXELS ? 0 : CG > 1 ? q & 3 : (q >> 2) & 3;
+  }
 
   __device__ __forceinline__ static void place(int i, int& row, int& px, int& cg) {
     cg = i % CG;
@@ -171,18 +189,20 @@ struct PixTile {  // ROWS x 4 QUADS pixels of C channels, held channel-major in 
       const int i = imin(threadIdx.x + j * 256, ITEMS - 1);
       int row, px, cg;
       place(i, row, px, cg);
-      const int gy = WRAP ? wrapi(y0 + row, H) : y0 + row;
+      const int gy = WRAP ? wrap_near(y0 + row, H) : y0 + row;
       const int gx = x0 + px;
       const bool rowin = gy < H;
       const bf16* src = img + (size_t)(rowin ? gy : 0) * W * C + cg * 8;
+      const int tn = turn(i);
       if (rowin && gx >= 0 && gx + 4 <= W) {
 #pragma unroll
-        for (int p = 0; p < 4; ++p) v[j][p] = *reinterpret_cast<const u32x4*>(src + (size_t)(gx + p) * C);
+        for (int p = 0; p < 4; ++p) v[j][p] = *reinterpret_cast<const u32x4*>(src + (size_t)(gx + (p ^ tn)) * C);
       } else {
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-          const bool in = WRAP || (rowin && gx + p < W);
-          const u32x4 r = *reinterpret_cast<const u32x4*>(src + (size_t)(in ? wrapi(gx + p, W) : 0) * C);
+          const int gp = gx + (p ^ tn);
+          const bool in = WRAP || (rowin && gp < W);
+          const u32x4 r = *reinterpret_cast<const u32x4*>(src + (size_t)(in ? wrap_near(gp, W) : 0) * C);
           v[j][p] = in ? r : u32x4{0, 0, 0, 0};
         }
       }
@@ -195,98 +215,53 @@ struct PixTile {  // ROWS x 4 QUADS pixels of C channels, held channel-major in 
       if (j * 256 + 256 > ITEMS && i >= ITEMS) continue;
       int row, px, cg;
       place(i, row, px, cg);
-      unsigned char* dst = lds + cg * 8 * CS + row * ROWB + px * 2;
+      const int tn = turn(i);
+      const unsigned low = tn & 1 ? 0x01000504 : 0x05040100, high = tn & 1 ? 0x03020706 : 0x07060302;
+      unsigned char* dst = lds + row * RP + (px & 4) * 2;
 #pragma unroll
       for (int c = 0; c < 4; ++c) {  // channels 2 c (low halves) and 2 c + 1 (high halves)
-        *reinterpret_cast<uint2*>(dst + 2 * c * CS) =
-            make_uint2(__builtin_amdgcn_perm(v[j][1][c], v[j][0][c], 0x05040100),
-                       __builtin_amdgcn_perm(v[j][3][c], v[j][2][c], 0x05040100));
-        *reinterpret_cast<uint2*>(dst + (2 * c + 1) * CS) =
-            make_uint2(__builtin_amdgcn_perm(v[j][1][c], v[j][0][c], 0x07060302),
-                       __builtin_amdgcn_perm(v[j][3][c], v[j][2][c], 0x07060302));
+        const u32x4 d = {__builtin_amdgcn_perm(v[j][1][c], v[j][0][c], low), __builtin_amdgcn_perm(v[j][3][c], v[j][2][c], low),
+                         __builtin_amdgcn_perm(v[j][1][c], v[j][0][c], high), __builtin_amdgcn_perm(v[j][3][c], v[j][2][c], high)};
+        *reinterpret_cast<uint2*>(dst + at(cg * 8 + 2 * c, px >> 3)) = tn & 2 ? make_uint2(d[1], d[0]) : make_uint2(d[0], d[1]);
+        *reinterpret_cast<uint2*>(dst + at(cg * 8 + 2 * c + 1, px >> 3)) = tn & 2 ? make_uint2(d[3], d[2]) : make_uint2(d[2], d[3]);
+      }
+    }
+  }
+  // the first LW columns as they came, pixel by pixel
+  template <int LW>
+  __device__ __forceinline__ void store_pixels(bf16* tile) const {
+#pragma unroll
+    for (int j = 0; j < NIT; ++j) {
+      const int i = threadIdx.x + j * 256;
+      if (j * 256 + 256 > ITEMS && i >= ITEMS) continue;
+      int row, px, cg;
+      place(i, row, px, cg);
+      const int tn = turn(i);
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const int x = px + (p ^ tn);
+        if (4 * QUADS <= LW || x < LW) *reinterpret_cast<u32x4*>(&tile[(row * LW + x) * C + pixel_chunk<C>(x, cg) * 8]) = v[j][p];
       }
     }
   }
 };
 
-template <int GC, int XC>
-__global__ void __launch_bounds__(256) k_wgrad_mfma(const bf16* g, const bf16* x, float* partial, int gcr, int xcr,
-                                                   int B, int H, int W) {
-  constexpr int MB = (GC + 15) / 16, NB = (XC + 15) / 16;
-  constexpr int PAIRS = MB * NB;  // 2 or 4
-  constexpr int RG = 4 / PAIRS;   // waves per pair
-  static_assert(PAIRS * RG == 4, "four waves per block");
-  static_assert(TH == 8 && TW == 32, "one K block per tile row");
-  using GT = PixTile<GC, TH, TW / 4, 2 * TW>;
-  using XT = PixTile<XC, TH + 2, (TW + 4) / 4, 80>;  // columns x0 - 1 .. x0 + 34 (the last two are not used)
-  constexpr int RED_BYTES = 2 * 64 * 40 * 4;         // accumulators of two waves
-  constexpr int TILE_BYTES = GT::BYTES + XT::BYTES;
-  __shared__ __attribute__((aligned(16))) unsigned char lds[TILE_BYTES > RED_BYTES ? TILE_BYTES : RED_BYTES];
-  unsigned char* gl = lds;
-  unsigned char* xl = lds + GT::BYTES;
-  const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int pair = wave % PAIRS, rg = wave / PAIRS;
-  const int mb = pair / NB, nb = pair - mb * NB;
-  const int m = lane & 15, kc = lane >> 4;
-  // channels beyond the tensor's give rows and columns that are not written
-  const unsigned char* ga = gl + ((mb * 16 + m) % GC) * GT::CS + kc * 16;
-  const unsigned char* xa = xl + ((nb * 16 + m) % XC) * XT::CS + kc * 16;
-  f32x4 acc[9], accb = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int tap = 0; tap < 9; ++tap) acc[tap] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const bf16x8 ones = {(bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f};
+// Pixels 0 .. 7, 1 .. 8 and 2 .. 9 from a chunk of a channel-major row and the next one.
+__device__ __forceinline__ void row_taps(const unsigned char* at, const unsigned char* next, bf16x8 (&f)[3]) {
+  const u32x4 d = *reinterpret_cast<const u32x4*>(at);
+  const unsigned e = *reinterpret_cast<const unsigned*>(next);
+  f[0] = __builtin_bit_cast(bf16x8, d);
+  f[1] = __builtin_bit_cast(bf16x8, u32x4{__builtin_amdgcn_alignbit(d[1], d[0], 16), __builtin_amdgcn_alignbit(d[2], d[1], 16),
+                                          __builtin_amdgcn_alignbit(d[3], d[2], 16), __builtin_amdgcn_alignbit(e, d[3], 16)});
+  f[2] = __builtin_bit_cast(bf16x8, u32x4{d[1], d[2], d[3], e});
+}
 
-  const int tiles_x = (W + TW - 1) / TW, tiles_y = (H + TH - 1) / TH;
-  const int ntiles = B * tiles_x * tiles_y;
-  const size_t plane = (size_t)H * W;
-  GT gt;
-  XT xt;
-  auto fetch = [&](int tile) {
-    const int img = tile / (tiles_x * tiles_y);
-    const int rem = tile - img * tiles_x * tiles_y;
-    const int ty = rem / tiles_x, tx = rem - ty * tiles_x;
-    gt.template fetch<false>(g + (size_t)img * plane * GC, H, W, ty * TH, tx * TW);
-    xt.template fetch<true>(x + (size_t)img * plane * XC, H, W, ty * TH - 1, tx * TW - 1);
-  };
-  if ((int)blockIdx.x < ntiles) fetch(blockIdx.x);
-  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    gt.store(gl);
-    xt.store(xl);
-    __syncthreads();
-    if (tile + (int)gridDim.x < ntiles) fetch(tile + gridDim.x);
-    // row r of x: ten pixels of this lane's channel, as the taps' three columns
-    auto xrow = [&](int r, bf16x8 (&f)[3]) {
-      const u32x4 d = *reinterpret_cast<const u32x4*>(xa + r * 80);
-      const unsigned e = *reinterpret_cast<const unsigned*>(xa + r * 80 + 16);
-      f[0] = __builtin_bit_cast(bf16x8, d);
-      f[1] = __builtin_bit_cast(bf16x8, u32x4{__builtin_amdgcn_alignbit(d[1], d[0], 16), __builtin_amdgcn_alignbit(d[2], d[1], 16),
-                                              __builtin_amdgcn_alignbit(d[3], d[2], 16), __builtin_amdgcn_alignbit(e, d[3], 16)});
-      f[2] = __builtin_bit_cast(bf16x8, u32x4{d[1], d[2], d[3], e});
-    };
-    bf16x8 xf[3][3];
-    if constexpr (RG == 1) {
-      xrow(0, xf[0]);
-      xrow(1, xf[1]);
-    }
-#pragma unroll
-    for (int p = 0; p < TH / RG; ++p) {
-      const int py = RG * p + rg;
-      if constexpr (RG == 1) {
-        xrow(p + 2, xf[(p + 2) % 3]);
-      } else {
-#pragma unroll
-        for (int ta = 0; ta < 3; ++ta) xrow(py + ta, xf[(p + ta) % 3]);
-      }
-      const bf16x8 a = *reinterpret_cast<const bf16x8*>(ga + py * (2 * TW));
-#pragma unroll
-      for (int tap = 0; tap < 9; ++tap)
-        acc[tap] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, xf[(p + tap / 3) % 3][tap % 3], acc[tap], 0, 0, 0);
-      if (nb == 0) accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ones, accb, 0, 0, 0);
-    }
-    __syncthreads();
-  }
-  // waves of the second row group hand their sums to the first
+// Sums of a block's waves over (16-row co block mb, 16-column ci block nb)
+// to its partial row; waves of a second row group hand theirs to the first.
+template <int PAIRS, int RG>
+__device__ __forceinline__ void write_partial(const f32x4 (&acc)[9], const f32x4& accb, unsigned char* lds, int pair,
+                                              int rg, int mb, int nb, int gcr, int xcr, float* out) {
+  const int lane = threadIdx.x & 63, m = lane & 15, kc = lane >> 4;
   float* red = reinterpret_cast<float*>(lds);
   if (RG == 2 && rg == 1) {
 #pragma unroll
@@ -296,29 +271,223 @@ __global__ void __launch_bounds__(256) k_wgrad_mfma(const bf16* g, const bf16* x
       red[((pair * 10 + 9) * 4 + i) * 64 + lane] = accb[i];
     }
   }
-  __syncthreads();
-  float* out = partial + (size_t)blockIdx.x * (size_t)(gcr * xcr * 9 + gcr);
-  if (rg == 0) {
-    const int ci = nb * 16 + m;
+  if (RG == 2) __syncthreads();
+  if (rg != 0) return;
+  const int ci = nb * 16 + m;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int co = mb * 16 + 4 * kc + i;
-      if (co >= gcr) continue;
-      if (ci < xcr) {
+  for (int i = 0; i < 4; ++i) {
+    const int co = mb * 16 + 4 * kc + i;
+    if (co >= gcr) continue;
+    if (ci < xcr) {
 #pragma unroll
-        for (int tap = 0; tap < 9; ++tap) {
-          float v = acc[tap][i];
-          if (RG == 2) v += red[((pair * 10 + tap) * 4 + i) * 64 + lane];
-          out[((size_t)co * xcr + ci) * 9 + tap] = v;
-        }
-      }
-      if (nb == 0 && m == 0) {
-        float v = accb[i];
-        if (RG == 2) v += red[((pair * 10 + 9) * 4 + i) * 64 + lane];
-        out[(size_t)gcr * xcr * 9 + co] = v;
+      for (int tap = 0; tap < 9; ++tap) {
+        float v = acc[tap][i];
+        if (RG == 2) v += red[((pair * 10 + tap) * 4 + i) * 64 + lane];
+        out[((size_t)co * xcr + ci) * 9 + tap] = v;
       }
     }
+    if (nb == 0 && m == 0) {
+      float v = accb[i];
+      if (RG == 2) v += red[((pair * 10 + 9) * 4 + i) * 64 + lane];
+      out[(size_t)gcr * xcr * 9 + co] = v;
+    }
   }
+}
+constexpr int kPartialLds = 2 * 64 * 40 * 4;  // bytes the above needs where RG is 2
+
+// The first layer, whose input needs no gradient: 32 channels of g, 8 of x.
+// 23 us for 16 crops of 256 x 256 (84 MB).
+__global__ void __launch_bounds__(256) k_wgrad_first(const bf16* g, const bf16* x, float* partial, int gcr, int xcr,
+                                                     int B, int H, int W) {
+  constexpr int GC = 32, XC = 8, PAIRS = 2, RG = 2;  // RG: waves per pair
+  static_assert(TH == 8 && TW == 32, "one K block per tile row");
+  using GT = PixTile<GC, TH, TW / 4>;
+  using XT = PixTile<XC, TH + 2, (TW + 4) / 4>;  // columns x0 - 1 .. x0 + 34 (the last two are not used)
+  constexpr int TILE_BYTES = GT::BYTES + XT::BYTES;
+  __shared__ __attribute__((aligned(16))) unsigned char lds[TILE_BYTES > kPartialLds ? TILE_BYTES : kPartialLds];
+  unsigned char* gl = lds;
+  unsigned char* xl = lds + GT::BYTES;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int mb = wave % PAIRS, rg = wave / PAIRS;
+  const int m = lane & 15, kc = lane >> 4;
+  // channels beyond the tensor's give columns that are not written
+  const unsigned char* ga = gl + GT::at(mb * 16 + m, kc);
+  const unsigned char* xa = xl + XT::at(m % XC, kc);
+  const unsigned char* xb = xl + XT::at(m % XC, kc + 1);
+  f32x4 acc[9], accb = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int tap = 0; tap < 9; ++tap) acc[tap] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const bf16x8 ones = {(bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f};
+
+  const TileGrid tg(B, H, W, TH, TW);
+  const size_t plane = (size_t)H * W;
+  GT gt;
+  XT xt;
+  auto fetch = [&](int tile) {
+    int img, y0, x0;
+    tg.origin(tile, img, y0, x0);
+    gt.template fetch<false>(g + (size_t)img * plane * GC, H, W, y0, x0);
+    xt.template fetch<true>(x + (size_t)img * plane * XC, H, W, y0 - 1, x0 - 1);
+  };
+  int t, t_end, step;
+  tg.span(t, t_end, step);
+  if (t < t_end) fetch(t);
+  for (; t < t_end; t += step) {
+    gt.store(gl);
+    xt.store(xl);
+    __syncthreads();
+    if (t + step < t_end) fetch(t + step);
+#pragma unroll
+    for (int p = 0; p < TH / RG; ++p) {
+      const int py = RG * p + rg;
+      bf16x8 xf[3][3];
+#pragma unroll
+      for (int ta = 0; ta < 3; ++ta) row_taps(xa + (py + ta) * XT::RP, xb + (py + ta) * XT::RP, xf[ta]);
+      const bf16x8 a = *reinterpret_cast<const bf16x8*>(ga + py * GT::RP);
+#pragma unroll
+      for (int tap = 0; tap < 9; ++tap)
+        acc[tap] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, xf[tap / 3][tap % 3], acc[tap], 0, 0, 0);
+      accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ones, accb, 0, 0, 0);
+    }
+    __syncthreads();
+  }
+  write_partial<PAIRS, RG>(acc, accb, lds, mb, rg, mb, 0, gcr, xcr,
+                           partial + (size_t)blockIdx.x * (size_t)(gcr * xcr * 9 + gcr));
+}
+
+// Backward of layers 1 .. 5 in one pass over g and x: the gradient flowing
+// into the layer before,
+//   out[q][ci] = [x[q][ci] > 0] sum_{co, tap} w[co][ci][tap] g[q - shift(tap)][co],
+// and the partial weight and bias gradients
+//   dW[co][ci][tap] = sum_q g[q - shift(tap)][co] x[q][ci].
+// Both read g around a tile of x, so that g and its halo are loaded once (as
+// two kernels they move 335 MB a 32-channel layer of 16 crops of 256 x 256,
+// as one 201 MB), and held twice in LDS: pixel by pixel as the operand of
+// the convolution, channel by channel as that of the weight gradient, of which
+// row p of x meets rows p .. p + 2.  x lies there channel by channel too, and
+// pixel by pixel as the mask.  79 KB: two blocks per CU, so that one's loads
+// and stores run beside the other's products.  Two waves share rows and halve
+// the channels of the convolution, which leaves its weights 36 registers; with
+// 72 the kernel spilled and took 78 us.  A 32-channel layer of those crops
+// took 40 us for the gradient of x and 41 for that of the weights; this takes
+// 63 (the 8-channel one 26 + 31, now 37): the products alone are 19 us, their
+// operands' packing as much again, and the LDS 20.
+struct BwdArgs {
+  const bf16* g;      // NHWC, GC channels
+  const bf16* x;      // NHWC, 32 channels: the layer's input, an activation after its ReLU
+  const bf16* wfrag;  // 32 x kpad(GC)
+  bf16* out;          // NHWC, 32 channels
+  float* partial;
+  int gcr;            // real channels of g
+  int B, H, W;
+};
+
+template <int GC>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_bwd(BwdArgs a) {
+  constexpr int XC = 32, LH = TH + 2, LW = TW + 2;
+  constexpr int MB = (GC + 15) / 16, PAIRS = 2 * MB, RG = 4 / PAIRS;
+  using GT = PixTile<GC, LH, (TW + 4) / 4, true>;
+  using XT = PixTile<XC, TH, TW / 4, true>;
+  constexpr int GPIX = LH * LW * GC * 2, XPIX = TH * TW * XC * 2;
+  constexpr int BYTES = GT::BYTES + XT::BYTES + GPIX + XPIX;
+  static_assert(BYTES <= 80 * 1024 && BYTES >= kPartialLds, "two blocks per CU");
+  __shared__ __attribute__((aligned(16))) unsigned char lds[BYTES];
+  unsigned char* gl = lds;
+  unsigned char* xl = gl + GT::BYTES;
+  bf16* gpix = reinterpret_cast<bf16*>(xl + XT::BYTES);
+  bf16* xpix = reinterpret_cast<bf16*>(xl + XT::BYTES + GPIX);
+  const int H = a.H, W = a.W;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int pair = wave % PAIRS, rg = wave / PAIRS;
+  const int mb = pair / 2, nb = pair % 2;
+  const int m = lane & 15, kc = lane >> 4;
+  const unsigned char* ga = gl + GT::at((mb * 16 + m) % GC, kc);
+  const unsigned char* gb = gl + GT::at((mb * 16 + m) % GC, kc + 1);
+  const unsigned char* xa = xl + XT::at(nb * 16 + m, kc);
+  const int cb = 16 * (wave & 1), row0 = 4 * (wave >> 1);  // this wave's channels and rows of the gradient of x
+  bf16x8 wf[1][kpad(GC) / 32];
+  load_wfrag<GC, 16>(a.wfrag + cb * kpad(GC), wf);
+  f32x4 acc[9], accb = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int tap = 0; tap < 9; ++tap) acc[tap] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  const TileGrid tg(a.B, H, W, TH, TW);
+  const size_t plane = (size_t)H * W;
+  int t, t_end, step;
+  tg.span(t, t_end, step);
+  GT gt;
+  XT xt;
+  auto fetch = [&](int tile) {
+    int img, y0, x0;
+    tg.origin(tile, img, y0, x0);
+    gt.template fetch<true>(a.g + (size_t)img * plane * GC, H, W, y0 - 1, x0 - 1);
+    xt.template fetch<false>(a.x + (size_t)img * plane * XC, H, W, y0, x0);
+  };
+  if (t < t_end) fetch(t);
+  for (; t < t_end; t += step) {
+    gt.store(gl);
+    gt.template store_pixels<LW>(gpix);
+    xt.store(xl);
+    xt.template store_pixels<TW>(xpix);
+    __syncthreads();
+    int img, y0, x0;
+    tg.origin(t, img, y0, x0);
+
+    // the gradient of x
+#pragma unroll 1  // unrolled, it spills
+    for (int h = 0; h < 4; h += 2) {
+      f32x4 d[2][2][1];
+      conv_mfma<GC, 16, LW, true>(gpix, wf, row0 + h, d);
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const int ly = row0 + h + r, y = y0 + ly;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          const int px = c * 16 + m;
+          if (y >= H || x0 + px >= W) continue;
+          const uint2 mraw = *reinterpret_cast<const uint2*>(&xpix[(ly * TW + px) * XC + pixel_chunk<XC>(px, (cb >> 3) + (kc >> 1)) * 8 + 4 * (kc & 1)]);
+          const bf16* mk = reinterpret_cast<const bf16*>(&mraw);
+          bf16 o[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[i] = f2bf(bf2f(mk[i]) > 0.0f ? d[r][c][0][i] : 0.0f);
+          *reinterpret_cast<uint2*>(&a.out[((size_t)img * plane + (size_t)y * W + x0 + px) * XC + cb + 4 * kc]) =
+              *reinterpret_cast<const uint2*>(o);
+        }
+      }
+    }
+    if (t + step < t_end) fetch(t + step);
+    // the gradient of the weights; pixels outside the image have x = 0, and
+    // are left out of the bias's by the column of ones
+    bf16x8 ones;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ones[i] = (bf16)(x0 + kc * 8 + i < W ? 1.0f : 0.0f);
+    bf16x8 gf[3][3];
+    if constexpr (RG == 1) {
+      row_taps(ga, gb, gf[0]);
+      row_taps(ga + GT::RP, gb + GT::RP, gf[1]);
+    }
+#pragma unroll
+    for (int p = 0; p < TH / RG; ++p) {
+      __builtin_amdgcn_sched_barrier(0);
+      const int py = RG * p + rg;
+      if constexpr (RG == 1) {
+        row_taps(ga + (p + 2) * GT::RP, gb + (p + 2) * GT::RP, gf[(p + 2) % 3]);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 3; ++r) row_taps(ga + (py + r) * GT::RP, gb + (py + r) * GT::RP, gf[(p + r) % 3]);
+      }
+      const bf16x8 b = *reinterpret_cast<const bf16x8*>(xa + py * XT::RP);
+      // tap (ta, tc) pairs x[q] with g[q - (ta - 1, tc - 1)]
+#pragma unroll
+      for (int tap = 0; tap < 9; ++tap)
+        acc[tap] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf[(p + 2 - tap / 3) % 3][2 - tap % 3], b, acc[tap], 0, 0, 0);
+      if (nb == 0 && y0 + py < H)
+        accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf[(p + 1) % 3][1], ones, accb, 0, 0, 0);
+    }
+    __syncthreads();
+  }
+  write_partial<PAIRS, RG>(acc, accb, lds, pair, rg, mb, nb, a.gcr, XC,
+                           a.partial + (size_t)blockIdx.x * (size_t)(a.gcr * XC * 9 + a.gcr));
 }
 
 // grad[k] = sum over blocks (fixed order) of partial[b][k].  A block sums 32
@@ -588,34 +757,32 @@ hipError_t run_backward(ils_net* n, const float* t, int B, int H, int W) {
   int cur = 0;
   for (int i = 5; i >= 0 && e == hipSuccess; --i) {
     const Layer& L = kNet.L[i];
-    const bf16* g = n->gbuf[cur];
-    const bf16* x = n->act[i];
     const int len = L.co * L.ci * 9 + L.co;
-    if (i == 5)
-      hipLaunchKernelGGL((k_wgrad_mfma<8, 32>), dim3(nblk), dim3(256), 0, st, g, x, n->partial, L.co, L.ci, B,
-                         H, W);
-    else if (i == 0)
-      hipLaunchKernelGGL((k_wgrad_mfma<32, 8>), dim3(nblk), dim3(256), 0, st, g, x, n->partial, L.co, L.ci, B,
-                         H, W);
-    else
-      hipLaunchKernelGGL((k_wgrad_mfma<32, 32>), dim3(nblk), dim3(256), 0, st, g, x, n->partial, L.co, L.ci,
-                         B, H, W);
+    if (i == 0) {
+      hipLaunchKernelGGL(k_wgrad_first, dim3(nblk), dim3(256), 0, st, n->gbuf[cur], n->act[0], n->partial, L.co,
+                         L.ci, B, H, W);
+    } else {
+      BwdArgs a{};
+      a.g = n->gbuf[cur];
+      a.x = n->act[i];
+      a.wfrag = n->wd[i];
+      a.out = n->gbuf[1 - cur];
+      a.partial = n->partial;
+      a.gcr = L.co;
+      a.B = B;
+      a.H = H;
+      a.W = W;
+      if (i == 5)
+        hipLaunchKernelGGL(k_bwd<8>, dim3(nblk), dim3(256), 0, st, a);
+      else
+        hipLaunchKernelGGL(k_bwd<32>, dim3(nblk), dim3(256), 0, st, a);
+      cur = 1 - cur;
+    }
     e = hipGetLastError();
     if (e != hipSuccess) break;
     hipLaunchKernelGGL(k_reduce_partials, dim3((len + kRedCols - 1) / kRedCols), dim3(kRedCols * kRedRows), 0, st,
                        n->partial, nblk, len, n->grad + L.w_off);
     e = hipGetLastError();
-    if (e != hipSuccess || i == 0) break;
-    ConvArgs a{};
-    a.in = g;
-    a.wfrag = n->wd[i];
-    a.out = n->gbuf[1 - cur];
-    a.mask = n->act[i];
-    a.B = B;
-    a.H = H;
-    a.W = W;
-    e = (i == 5) ? conv<8, 32, CONV_DGRAD>(a, st) : conv<32, 32, CONV_DGRAD>(a, st);
-    cur = 1 - cur;
   }
   return e;
 }

@@ -35,7 +35,7 @@ constexpr int TH = 8;   // output rows per convolution block (2 per wave)
 constexpr int TW = 32;  // output columns per block (2 blocks of 16 pixels)
 constexpr int NTHREADS = 256;
 
-enum ConvMode : int { CONV_RELU = 0, CONV_LAST = 1, CONV_DGRAD = 2 };
+enum ConvMode : int { CONV_RELU = 0, CONV_LAST = 1 };
 
 __host__ __device__ constexpr int kpad(int cip) { return (9 * cip + 31) / 32 * 32; }
 
@@ -55,12 +55,17 @@ __device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
 // v mod n for -n <= v < 2n.
 __device__ __forceinline__ int wrap1(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
 
+// v mod n for any v, without the division where v is within a period of [0, n).
+__device__ __forceinline__ int wrap_near(int v, int n) {
+  const int r = wrap1(v, n);
+  return (unsigned)r < (unsigned)n ? r : wrapi(v, n);
+}
+
 struct ConvArgs {
   const bf16* in;       // NHWC, CIP channels
   const bf16* wfrag;    // COP x KP
-  const float* bias;    // COP (zeros past the layer's channels); unused for DGRAD
-  bf16* out;            // NHWC, COP channels (RELU, DGRAD)
-  const bf16* mask;     // DGRAD: forward activation at this position (NHWC, COP channels)
+  const float* bias;    // COP (zeros past the layer's channels)
+  bf16* out;            // NHWC, COP channels (RELU)
   const float* f;       // LAST: planar fp32 input image (B, 3, H, W)
   float* v;             // LAST: planar fp32 output (B, 3, H, W)
   int B, H, W;
@@ -166,10 +171,18 @@ __device__ __forceinline__ void load_wfrag(const bf16* wfrag, bf16x8 (&wf)[COP /
       wf[mb][kb] = *reinterpret_cast<const bf16x8*>(&wfrag[(mb * 16 + (lane & 15)) * KP + kb * 32 + (lane >> 4) * 8]);
 }
 
+// The place in its pixel of 16-byte chunk c of the pixel in column x.  Every
+// second quad of columns has the halves of its pixels swapped, so that the
+// lanes a 16-byte LDS read serves together fall on different banks.
+template <int CIP>
+__device__ __forceinline__ int pixel_chunk(int x, int c) {
+  return CIP == 32 ? c ^ ((x >> 1) & 2) : c;
+}
+
 // acc[r][nb][mb] = W x X for the output pixels (row0 + r, 16 nb + lane % 16)
 // of a tile in LDS whose rows are LW pixels of CIP channels; the tap (a, c)
 // of output (y, x) reads tile pixel (y + a, x + c).
-template <int CIP, int COP, int LW>
+template <int CIP, int COP, int LW, bool SWAP = false>
 __device__ __forceinline__ void conv_mfma(const bf16* tile, const bf16x8 (&wf)[COP / 16][kpad(CIP) / 32], int row0,
                                           f32x4 (&acc)[2][2][COP / 16]) {
   constexpr int KB = kpad(CIP) / 32;
@@ -199,7 +212,7 @@ __device__ __forceinline__ void conv_mfma(const bf16* tile, const bf16x8 (&wf)[C
       for (int nb = 0; nb < 2; ++nb) {
         const int ly = row0 + r + ta;
         const int lx = nb * 16 + (lane & 15) + tc;
-        const bf16x8 bfr = *reinterpret_cast<const bf16x8*>(&tile[(ly * LW + lx) * CIP + chunk * 8]);
+        const bf16x8 bfr = *reinterpret_cast<const bf16x8*>(&tile[(ly * LW + lx) * CIP + (SWAP ? pixel_chunk<CIP>(lx, chunk) : chunk) * 8]);
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
           acc[r][nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[mb][kb], bfr, acc[r][nb][mb], 0, 0, 0);
@@ -236,7 +249,7 @@ __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(M
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) bias[mb][i] = (MODE == CONV_DGRAD) ? 0.0f : a.bias[mb * 16 + 4 * (lane >> 4) + i];
+    for (int i = 0; i < 4; ++i) bias[mb][i] = a.bias[mb * 16 + 4 * (lane >> 4) + i];
   st[0].store(tile);
   __syncthreads();
   // Every prefetch is issued (past the end it repeats the last tile), so
@@ -266,20 +279,6 @@ __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(M
           for (int i = 0; i < 3; ++i) fpix[r][nb][i] = in ? a.f[base + i * plane] : 0.0f;
         }
     }
-    // CONV_DGRAD: the activations behind the mask, likewise
-    uint2 mraw[2][2][MB];
-    if constexpr (MODE == CONV_DGRAD) {
-#pragma unroll
-      for (int r = 0; r < 2; ++r)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-          const int y = imin(y0 + wave * 2 + r, H - 1), x = imin(x0 + nb * 16 + (lane & 15), W - 1);
-          const size_t pix = (size_t)img * plane + (size_t)y * W + x;
-#pragma unroll
-          for (int mb = 0; mb < MB; ++mb)
-            mraw[r][nb][mb] = *reinterpret_cast<const uint2*>(&a.mask[pix * COP + mb * 16 + 4 * (lane >> 4)]);
-        }
-    }
     f32x4 acc[2][2][MB];
     conv_mfma<CIP, COP, LW>(tile + cur * TILE, wf, wave * 2, acc);
     if (t + G < t_end) nx.store(tile + (cur ^ 1) * TILE);
@@ -301,12 +300,6 @@ __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(M
             bf16 o[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) o[i] = f2bf(fmaxf(d[i] + bias[mb][i], 0.0f));
-            *reinterpret_cast<uint2*>(&a.out[pix * COP + co0]) = *reinterpret_cast<const uint2*>(o);
-          } else if constexpr (MODE == CONV_DGRAD) {
-            const bf16* m = reinterpret_cast<const bf16*>(&mraw[r][nb][mb]);
-            bf16 o[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = f2bf(bf2f(m[i]) > 0.0f ? d[i] : 0.0f);
             *reinterpret_cast<uint2*>(&a.out[pix * COP + co0]) = *reinterpret_cast<const uint2*>(o);
           } else {  // CONV_LAST: v = f + z for the three image channels
             if (co0 == 0) {
