@@ -225,8 +225,8 @@ int ils_iterate_from_c(ils_plan* plan, const float* f, const float* u0, int H, i
  * enqueue: frames of equal size, N and penalty form a class, run with one
  * launch per pass over a part of the class (one part per frame for frames
  * of one channel count with at least 4 Mi pixel-channels each, else two
- * parts); the parts form two independent chains of passes, the whole
- * sequence replayed as one HIP graph (unless ILS_PLAN_NO_GRAPH or pass
+ * parts); the parts are dealt by their work to two independent chains of
+ * passes, the whole sequence replayed as one HIP graph (unless ILS_PLAN_NO_GRAPH or pass
  * timing is active).  Results are bitwise those of one ils_smooth (or
  * ils_iterate_from, when u0 is set) per frame.  frames is a host array,
  * read during the call.  Each frame obeys the rules of ils_smooth.  Returns
@@ -298,10 +298,10 @@ int ils_plan_set_shapes(ils_plan* plan, int H, int W, int C, int row_shape, int 
 /* ---- allocation-free smoothing ----
  * For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
- * computation of ils_smooth (Algorithm 1, no plan, default tile shapes)
+ * computation of ils_smooth (Algorithm 1, no plan, tile shapes by rule)
  * with its two half spectra in a file-scope device array of the library
- * (64 MiB per GPU, held from the library's loading until the process ends)
- * instead of a caller workspace (its first 4 MiB hold the transform tables
+ * (66 MiB per GPU, held from the library's loading until the process ends)
+ * instead of a caller workspace (its first 6 MiB hold the transform tables
  * of every supported length).  The first call on a device copies the tables
  * into that array synchronously; later calls only enqueue on hip_stream.
  * No call allocates or frees memory.

@@ -1,5 +1,6 @@
-// Passes for transform lengths without a compiled four-step split: every
-// 2/3/5-smooth row length W/2 and column length H up to 4096.
+// Passes for frames of which a transform length (W/2 or H) has no compiled
+// four-step split: 2187, 3125, 3645 and 4000, whose smaller factor would not
+// fit the compiled passes' registers.
 //
 // The arithmetic is that of the compiled passes (Algorithm 1 with the
 // one-FFT right-hand side of Eq. (9), Sec. 3.2); the transforms are mixed-

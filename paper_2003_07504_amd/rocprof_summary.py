@@ -22,14 +22,14 @@ import sqlite3
 from .build import source_hash
 
 COPY_BYTES = 1 << 29
-KINDS = {"0": "row_first", "1": "row_mid", "2": "row_final", "3": "row_first"}
+KINDS = {"0": "row_first", "1": "row_mid", "2": "row_final"}
 
 
 def kind_of(name: str) -> str:
     m = re.search(r"k_row<(\d+), (\d+), (\d+), (\d), (\d)>", name)
     if m:
         return KINDS[m.group(4)] + ("_welsch" if m.group(5) == "1" else "")
-    if re.search(r"k_col<", name):
+    if re.search(r"k_col3?<", name):
         return "column"
     if "copyBuffer" in name:
         return "copy"
