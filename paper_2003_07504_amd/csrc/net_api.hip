@@ -3,6 +3,7 @@
 // that falls back to plain ILS.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -54,7 +55,8 @@ inline int gchan(int i) { return kNet.L[i].co == 3 ? 8 : 32; }
 
 inline size_t al(size_t v) { return (v + 255) / 256 * 256; }
 
-constexpr int kWgradBlocks = 512;
+constexpr int kWgradBlocks = 512;  // most blocks of a backward kernel (each writes a row of partial sums)
+constexpr int kPartialRows = 256;  // rows of a 32 -> 32 layer that the workspace holds (see net_layout)
 constexpr int kLossBlocks = 256;
 
 // --------------------------------------------------------- small kernels
@@ -590,7 +592,10 @@ struct ils_net {
   bf16* act[6];   // act[0] = x0 (8 ch), act[1..5] = a1..a5 (32 ch)
   bf16* gbuf[2];  // gradient ping-pong (32 ch)
   float* zbuf;    // v (B, 3, H, W) scratch
-  float* partial; // wgrad partials
+  // rows of partial sums: of layer 5, and of the layers before it
+  float* partial;
+  float* partial_wide;
+  size_t partial_bytes, partial_wide_bytes;
   double* lpart;  // loss partials
   float* loss;
 };
@@ -615,10 +620,16 @@ size_t net_layout(int B, int H, int W, ils_net* n) {
   }
   size_t o_act[6];
   o_act[0] = take(px * 8 * 2);
-  for (int i = 1; i < 6; ++i) o_act[i] = take(px * 32 * 2);
+  for (int i = 1; i < 5; ++i) o_act[i] = take(px * 32 * 2);
   size_t o_gb0 = take(px * 32 * 2), o_gb1 = take(px * 32 * 2);
+  // The last activation, v and the partial sums lie together: behind layer 5
+  // the first two are spent, and the partial sums of the layers before it
+  // start where they did, so that kWgradBlocks rows of a 32 -> 32 layer fit
+  // an area of kPartialRows of them for any batch of so many full tiles.
+  o_act[5] = take(px * 32 * 2);
   size_t o_z = take(px * 3 * 4);
-  size_t o_part = take((size_t)kWgradBlocks * (32 * 32 * 9 + 32) * 4);
+  size_t o_part = take((size_t)kPartialRows * (32 * 32 * 9 + 32) * 4);
+  const size_t e_part = off;
   size_t o_lp = take(kLossBlocks * 8);
   size_t o_loss = take(4);
   if (n) {
@@ -637,6 +648,9 @@ size_t net_layout(int B, int H, int W, ils_net* n) {
     n->gbuf[1] = (bf16*)(b + o_gb1);
     n->zbuf = (float*)(b + o_z);
     n->partial = (float*)(b + o_part);
+    n->partial_bytes = e_part - o_part;
+    n->partial_wide = (float*)(b + o_act[5]);
+    n->partial_wide_bytes = e_part - o_act[5];
     n->lpart = (double*)(b + o_lp);
     n->loss = (float*)(b + o_loss);
   }
@@ -754,15 +768,18 @@ hipError_t run_backward(ils_net* n, const float* t, int B, int H, int W) {
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kLossBlocks), 0, st, n->lpart, 3.0 * (double)px, n->loss);
   e = hipGetLastError();
-  // no more blocks (partial rows to write and to sum) than there are tiles
   const long long tiles = (long long)B * ((H + TH - 1) / TH) * ((W + TW - 1) / TW);
-  const int nblk = (int)(tiles < kWgradBlocks ? tiles : kWgradBlocks);
   int cur = 0;
   for (int i = 5; i >= 0 && e == hipSuccess; --i) {
     const Layer& L = kNet.L[i];
     const int len = L.co * L.ci * 9 + L.co;
+    // no more blocks (partial rows to write and to sum) than there are tiles,
+    // nor than rows fit
+    float* partial = i == 5 ? n->partial : n->partial_wide;
+    const long long rows = (long long)((i == 5 ? n->partial_bytes : n->partial_wide_bytes) / ((size_t)len * 4));
+    const int nblk = (int)std::min({tiles, rows, (long long)kWgradBlocks});
     if (i == 0) {
-      hipLaunchKernelGGL(k_wgrad_first, dim3(nblk), dim3(256), 0, st, n->gbuf[cur], n->act[0], n->partial, L.co,
+      hipLaunchKernelGGL(k_wgrad_first, dim3(nblk), dim3(256), 0, st, n->gbuf[cur], n->act[0], partial, L.co,
                          L.ci, B, H, W);
     } else {
       BwdArgs a{};
@@ -770,7 +787,7 @@ hipError_t run_backward(ils_net* n, const float* t, int B, int H, int W) {
       a.x = n->act[i];
       a.wfrag = n->wd[i];
       a.out = n->gbuf[1 - cur];
-      a.partial = n->partial;
+      a.partial = partial;
       a.gcr = L.co;
       a.B = B;
       a.H = H;
@@ -784,7 +801,7 @@ hipError_t run_backward(ils_net* n, const float* t, int B, int H, int W) {
     e = hipGetLastError();
     if (e != hipSuccess) break;
     hipLaunchKernelGGL(k_reduce_partials, dim3((len + kRedCols - 1) / kRedCols), dim3(kRedCols * kRedRows), 0, st,
-                       n->partial, nblk, len, n->grad + L.w_off);
+                       partial, nblk, len, n->grad + L.w_off);
     e = hipGetLastError();
   }
   return e;
