@@ -19,6 +19,7 @@
 
 #include "../../include/ils.h"
 #include "ils_launch.hpp"
+#include "ils_scale.hpp"
 
 using ilsk::WorkList;
 using ilsk::cf;
@@ -242,34 +243,10 @@ static int check_size(const ils_plan* plan, int H, int W, int C) {
   return ILS_OK;
 }
 
-// kappa and the scale s of the iterate (see FrameDesc); d.H and d.W are set.
-// A rounding error of s / (2 H W) times 1 / s would scale the whole result,
-// so 1 / s is taken among the floats within three units in the last place of
-// it, where that product is nearest to 1 / (2 H W).
-static void set_scale(FrameDesc& d, double kappa, double s) {
-  const double hw2 = 2.0 * (double)d.H * (double)d.W;
-  float c = (float)(1.0 / s);
-  for (int i = 0; i < 3; ++i) c = std::nextafter(c, 0.0f);
-  double best = HUGE_VAL;
-  for (int i = -3; i <= 3; ++i, c = std::nextafter(c, HUGE_VALF)) {
-    const float col = (float)(1.0 / (hw2 * (double)c));
-    const double off = std::fabs((double)col * (double)c * hw2 - 1.0);
-    if (off < best) {
-      best = off;
-      d.u_unscale = c;
-      d.col_scale = col;
-    }
-  }
-  d.kappa = (float)kappa;
-  d.u_scale = (float)(1.0 / (double)d.u_unscale);
-  d.kappa_mu = (float)(kappa * (double)d.u_unscale);
-}
-
-// Fill a descriptor for one frame; the caller sets f/u0/out and the
-// spectrum pointers.
-static void fill_desc_on(const char* tables, const std::map<int, LenTables>& tab, FrameDesc& d, int H, int W,
-                         int C, float lambda, float p, float eps) {
-  const double c0 = (double)p * std::pow((double)eps, (double)p / 2.0 - 1.0);  // Eq. (11)
+// Fill a descriptor for one frame; the caller sets the penalty (ils_scale.hpp),
+// f/u0/out and the spectrum pointers.
+static void fill_size_on(const char* tables, const std::map<int, LenTables>& tab, FrameDesc& d, int H, int W,
+                         int C) {
   const int M = W / 2;
   const LenTables& tr = tab.at(M);
   const LenTables& tc = tab.at(H);
@@ -284,27 +261,23 @@ static void fill_desc_on(const char* tables, const std::map<int, LenTables>& tab
   d.W = W;
   d.C = C;
   d.ldS = spec_ld(W);
-  d.a_exp = (float)((double)p / 2.0 - 1.0);
-  d.log2_r = 0.0f;
-  set_scale(d, (double)lambda * c0 / 2.0, 1.0 / std::sqrt((double)eps));
   d.boost = 0.0f;
   d.nb_row = 0;
+}
+static void fill_desc_on(const char* tables, const std::map<int, LenTables>& tab, FrameDesc& d, int H, int W,
+                         int C, float lambda, float p, float eps) {
+  fill_size_on(tables, tab, d, H, W, C);
+  const double c0 = (double)p * std::pow((double)eps, (double)p / 2.0 - 1.0);  // Eq. (11)
+  ilsk::set_charbonnier(d, lambda, p, eps, 1.0, c0);
 }
 static void fill_desc(const ils_plan* plan, FrameDesc& d, int H, int W, int C, float lambda, float p, float eps) {
   fill_desc_on(plan->tables, *plan->tab, d, H, W, C, lambda, p, eps);
 }
 
-// Welsch penalty (Sec. 5): c = c0 = 2 (Eq. (20)), so kappa = lambda; the
-// iterate's scale makes exp(-g^2 / (2 gamma^2)) a power of two of -(s g)^2.
-// s is kept within 2^-60 .. 2^60: beyond, gamma is so far from any image's
-// differences that mu is 0 (or the difference itself) either way.
 static void fill_desc_welsch(const ils_plan* plan, FrameDesc& d, int H, int W, int C, float lambda,
                              float gamma) {
-  fill_desc(plan, d, H, W, C, 1.0f, 1.0f, 1.0f);
-  const double w = std::sqrt(1.4426950408889634 / 2.0) / (double)gamma;
-  d.a_exp = 0.0f;
-  d.log2_r = 0.0f;
-  set_scale(d, (double)lambda, std::min(std::max(w, std::ldexp(1.0, -60)), std::ldexp(1.0, 60)));
+  fill_size_on(plan->tables, *plan->tab, d, H, W, C);
+  ilsk::set_welsch(d, lambda, gamma);
 }
 
 // Tables of every supported length, computed in double and rounded once to
@@ -913,10 +886,7 @@ int ils_iterate_from_c(ils_plan* plan, const float* f, const float* u0, int H, i
   FrameDesc d;
   fill_desc(plan, d, H, W, C, lambda, p, eps);
   // c within float rounding of c0 is c0 itself (the default path, bit for bit)
-  if (std::fabs((double)c - c0) > 1e-6 * c0) {
-    set_scale(d, (double)lambda * (double)c / 2.0, 1.0 / std::sqrt((double)eps));
-    d.log2_r = (float)std::log2(c0 / (double)c);
-  }
+  if (std::fabs((double)c - c0) > 1e-6 * c0) ilsk::set_charbonnier(d, lambda, p, eps, c0 / (double)c, c);
   d.f = f;
   d.u0 = u0;
   d.out = out;

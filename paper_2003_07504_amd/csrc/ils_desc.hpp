@@ -54,12 +54,14 @@ struct FrameDesc {
   float kappa;      // lambda * c / 2, c >= c0 = p eps^(p/2 - 1) (Welsch: c = 2)
   // Between passes the iterate is kept as s u, s = eps^(-1/2) (Welsch: s =
   // sqrt(log2(e) / 2) / gamma), so that the penalty's argument g^2 / eps is
-  // the square of a difference as it stands.
+  // the square of a difference as it stands (see set_charbonnier and
+  // set_welsch).
   float u_scale;    // s
   float u_unscale;  // 1 / s, applied by the final pass
   float kappa_mu;   // kappa / s: weight of D^T mu(s u) in the right-hand side
   float a_exp;      // p/2 - 1 (Welsch: unused)
-  float log2_r;     // log2(c0 / c): 0 for the paper's c = c0
+  float pen_k;      // eps s^2: 1, but at the limits of s (Welsch: unused)
+  float log2_r;     // log2(c0 / c) - a_exp log2(pen_k) (Welsch: unused)
   float col_scale;  // s / (2 H W): inverse-transform normalisation (and the
                     // factor 2 the row R2C leaves in its output)
   float boost;      // final pass writes u + boost (f - u) when non-zero

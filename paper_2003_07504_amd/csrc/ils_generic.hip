@@ -108,14 +108,15 @@ __global__ void __launch_bounds__(kGenThreads) k_gen_rhs(WorkList wl) {
   const ILS_G float* uu = u + (size_t)wrap(y - 1, H) * W;
   const ILS_G float* ud = u + (size_t)wrap(y + 1, H) * W;
   const ILS_G float* fr = gm(d.f) + (size_t)ch * H * W + (size_t)y * W;
-  const float a_exp = d.a_exp, kappa = d.kappa_mu, l2r = d.log2_r;
+  const MuConst mc{d.a_exp, d.pen_k, d.log2_r};
+  const float kappa = d.kappa_mu;
   const float us = FROM_A ? 1.0f : d.u_scale;  // the first half spectrum holds s u already
   auto r_at = [&](int x) {
     const float c = us * uc[x];
-    const float mxl = mu_pen<PEN>(c - us * uc[wrap(x - 1, W)], a_exp, l2r);
-    const float mx0 = mu_pen<PEN>(us * uc[wrap(x + 1, W)] - c, a_exp, l2r);
-    const float myu = mu_pen<PEN>(c - us * uu[x], a_exp, l2r);
-    const float my0 = mu_pen<PEN>(us * ud[x] - c, a_exp, l2r);
+    const float mxl = mu_pen<PEN>(c - us * uc[wrap(x - 1, W)], mc);
+    const float mx0 = mu_pen<PEN>(us * uc[wrap(x + 1, W)] - c, mc);
+    const float myu = mu_pen<PEN>(c - us * uu[x], mc);
+    const float my0 = mu_pen<PEN>(us * ud[x] - c, mc);
     return fmaf(kappa, (mxl - mx0) + (myu - my0), fr[x]);
   };
   for (int j = threadIdx.x; j < M; j += blockDim.x) buf[0][j] = cf{r_at(2 * j), r_at(2 * j + 1)};

@@ -28,32 +28,34 @@ namespace ilsk {
 constexpr int imax_c(int a, int b) { return a > b ? a : b; }
 
 // Normalised half-quadratic variable  mu / c = g (1 - (c0/c) (1 + g^2/eps)^(p/2 - 1))
-// (Eq. (7) divided by c, c0 = p eps^(p/2-1)), for a difference h = g / sqrt(eps)
-// of the scaled iterate: returns mu / (c sqrt(eps)).  Base-2 log/exp on the
-// hardware transcendental unit.  l2r = log2(c0 / c) is 0 for c = c0.
-__device__ __forceinline__ float mu_ns(float h, float a_exp, float l2r) {
-  float t = fmaf(h, h, 1.0f);
+// (Eq. (7) divided by c, c0 = p eps^(p/2-1)), for a difference h = s g of the
+// scaled iterate: returns s mu / c (k, l2r: see FrameDesc).  Base-2 log/exp on
+// the hardware transcendental unit.
+__device__ __forceinline__ float mu_ns(float h, float a_exp, float k, float l2r) {
+  float t = fmaf(h, h, k);
   float pw = __builtin_amdgcn_exp2f(fmaf(a_exp, __builtin_amdgcn_logf(t), l2r));
   return fmaf(-h, pw, h);
 }
 
 // Welsch penalty (Sec. 5, Eqs. (18)-(20)): with c = c0 = 2 the normalised
-// variable is mu / c = g (1 - exp(-g^2 / (2 gamma^2))); h = g sqrt(log2(e) / 2) / gamma.
-__device__ __forceinline__ float mu_ns_welsch(float h, float l2r) {
-  return fmaf(-h, __builtin_amdgcn_exp2f(fmaf(-h, h, l2r)), h);
+// variable is mu / c = g (1 - exp(-g^2 / (2 gamma^2))).
+__device__ __forceinline__ float mu_ns_welsch(float h) {
+  return fmaf(-h, __builtin_amdgcn_exp2f(-h * h), h);
 }
 
 enum Penalty : int { PEN_CHARBONNIER = 0, PEN_WELSCH = 1 };
 
-// mu / c of a scaled difference for the penalty of the kernel instance: a =
-// p/2 - 1 for the generalised Charbonnier penalty (Welsch: unused); l2r =
-// log2(c0 / c).
+// The penalty's constants of a frame (uniform), and s mu / c of a scaled
+// difference for the penalty of the kernel instance.
+struct MuConst {
+  float a_exp, k, l2r;
+};
 template <int PEN>
-__device__ __forceinline__ float mu_pen(float h, float a, float l2r) {
+__device__ __forceinline__ float mu_pen(float h, const MuConst& m) {
   if constexpr (PEN == PEN_WELSCH)
-    return mu_ns_welsch(h, l2r);
+    return mu_ns_welsch(h);
   else
-    return mu_ns(h, a, l2r);
+    return mu_ns(h, m.a_exp, m.k, m.l2r);
 }
 
 // Cross-lane moves inside a wavefront (no LDS allocation): the value of the
@@ -487,7 +489,8 @@ __device__ __forceinline__ void row_body(const FrameDesc& d, int band, int ch, f
   if (st_slot) {
     const float2* uc = reinterpret_cast<const float2*>(sl);
     const float2* ud = reinterpret_cast<const float2*>(sl + SLOT_F);
-    const float a_exp = d.a_exp, kappa = d.kappa_mu, l2r = d.log2_r;
+    const MuConst mc{d.a_exp, d.pen_k, d.log2_r};
+    const float kappa = d.kappa_mu;
     float mx1_prev = 0.0f;
     static_for<P>([&](auto n1c) {
       constexpr int n1 = decltype(n1c)::value;
@@ -512,9 +515,9 @@ __device__ __forceinline__ void row_body(const FrameDesc& d, int band, int ch, f
         right = uc[jp].x;
       }
       const float2 dn = ud[j];
-      myd[n1] = make_float2(mu_pen<PEN>(dn.x - c.x, a_exp, l2r), mu_pen<PEN>(dn.y - c.y, a_exp, l2r));
-      const float mx0 = mu_pen<PEN>(c.y - c.x, a_exp, l2r);
-      const float mx1 = mu_pen<PEN>(right - c.y, a_exp, l2r);
+      myd[n1] = make_float2(mu_pen<PEN>(dn.x - c.x, mc), mu_pen<PEN>(dn.y - c.y, mc));
+      const float mx0 = mu_pen<PEN>(c.y - c.x, mc);
+      const float mx1 = mu_pen<PEN>(right - c.y, mc);
       float mxl;
       if constexpr (kLaneReuse && n1 > 0) {
         const float sh = from_prev_lane(mx1);
@@ -522,7 +525,7 @@ __device__ __forceinline__ void row_body(const FrameDesc& d, int band, int ch, f
         mxl = (t == 0) ? wr : sh;
       } else {
         const int jm = (j == 0) ? M - 1 : j - 1;
-        mxl = mu_pen<PEN>(c.x - uc[jm].y, a_exp, l2r);
+        mxl = mu_pen<PEN>(c.x - uc[jm].y, mc);
       }
       mx1_prev = mx1;
       r[n1] = {fmaf(kappa, (mxl - mx0) - myd[n1].x, fv[n1].x), fmaf(kappa, (mx0 - mx1) - myd[n1].y, fv[n1].y)};
