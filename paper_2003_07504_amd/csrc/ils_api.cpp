@@ -1053,16 +1053,17 @@ int ils_tone_map_multiscale(ils_plan* plan, const float* f, int H, int W, const 
   float* scale = scratch + 2 * 256;
   const float* B[ILS_MAX_SCALES];
   // Every level is smoothed from L itself (not from the previous level), so
-  // they run as a batch of frames of one plane: one sequence of passes with
-  // K times the blocks per launch.  L then sits in
-  // out's first plane and a group's levels replace its first half spectra
-  // (dead by the final pass; the runtime-length final pass reads the second
-  // half spectra too); when the workspace holds the spectra of fewer than K
-  // levels, the first two go first, into out's other planes.  In place, or with a level that is L itself (N = 0 or lambda = 0), the
-  // levels run one after another in the workspace.  (1080p, three levels:
-  // whole call 420 -> 207 us.)
+  // they run as a batch of frames of one plane: one sequence of passes with K
+  // times the blocks per launch (1080p, three levels: whole call 420 -> 207 us).
+  // L then sits in out's first plane and a group's levels replace its first
+  // half spectra (dead by the final pass; the runtime-length final pass reads
+  // the second half spectra too); when the workspace holds the spectra of
+  // fewer than K levels, the first two go first, into out's other planes.  In
+  // place, with a level that is L itself (N = 0 or lambda = 0), or where out
+  // does not start at a multiple of 8 bytes, which the passes' loads of L
+  // expect, the levels run one after another in the workspace.
   auto fits = [&](int n) { return plan->ws_bytes >= kBatchHeaderBytes + frame_ws_bytes(H, W, n); };
-  const bool apart = out + 3 * plane <= f || f + 3 * plane <= out;
+  const bool apart = (out + 3 * plane <= f || f + 3 * plane <= out) && ((uintptr_t)out & 7) == 0;
   bool smooths = K > 1 && N > 0;
   for (int k = 0; k < K; ++k) smooths = smooths && lambdas[k] != 0.0f;
   const bool grouped = apart && smooths && fits(K <= 2 ? K : 2);

@@ -249,7 +249,8 @@ __device__ __forceinline__ const ILS_G E& at(const ILS_G void* base, unsigned of
 // wide) 17.4 -> 15.9; 4K MID 128 -> 123.  Only for stores that fill (nearly)
 // whole lines: with column tiles of 8 or 4, half and quarter lines that the
 // L2 would have gathered, the pass gets slower (4K, 8 wide: 65 -> 68 us; 4
-// wide: 62 -> 77), so those stay ordinary stores.
+// wide: 62 -> 77), so those stay ordinary stores.  The address must be a
+// multiple of 8, which a caller's image need not be.
 template <bool THROUGH>
 __device__ __forceinline__ void put(ILS_G void* base, unsigned off, cf v) {
   ILS_G unsigned long long* p =
@@ -624,18 +625,28 @@ __device__ __forceinline__ void row_final_body(const FrameDesc& d, int band, int
     ILS_G float* och = gm(d.out) + (size_t)ch * H * W;
     const unsigned off = 4u * (unsigned)(yrow * W) + 8u * (unsigned)lane;
     const float k = d.boost, us = d.u_unscale;
+    static_for<P>([&](auto n1c) {
+      constexpr int n1 = decltype(n1c)::value;
+      z[n1] = cf{us * z[n1].x, us * z[n1].y};
+    });
     if (k != 0.0f) {  // detail enhancement: u + k (f - u); each element is read before it is written
       const ILS_G float* fch = gm(d.f) + (size_t)ch * H * W;
       static_for<P>([&](auto n1c) {
         constexpr int n1 = decltype(n1c)::value;
         const float2 fv = float2(at<float2>(fch + 2 * Q * n1, off));
-        const float x = us * z[n1].x, y = us * z[n1].y;
-        put<true>(och + 2 * Q * n1, off, cf{fmaf(k, fv.x - x, x), fmaf(k, fv.y - y, y)});
+        z[n1] = cf{fmaf(k, fv.x - z[n1].x, z[n1].x), fmaf(k, fv.y - z[n1].y, z[n1].y)};
       });
-    } else {
+    }
+    if (((uintptr_t)d.out & 7) == 0) {
       static_for<P>([&](auto n1c) {
         constexpr int n1 = decltype(n1c)::value;
-        put<true>(och + 2 * Q * n1, off, cf{us * z[n1].x, us * z[n1].y});
+        put<true>(och + 2 * Q * n1, off, z[n1]);
+      });
+    } else {  // an image that starts at an odd float: no 8-byte store fits
+      static_for<P>([&](auto n1c) {
+        constexpr int n1 = decltype(n1c)::value;
+        at<float>(och + 2 * Q * n1, off) = z[n1].x;
+        at<float>(och + 2 * Q * n1, off + 4u) = z[n1].y;
       });
     }
   }
