@@ -193,7 +193,8 @@ __global__ void __launch_bounds__(kThreads) k_minmax_partial(const float* __rest
 // detail layers D_1 = L - B_1, D_i = B_{i-1} - B_i kept times w_i, base B_K
 // compressed: out_c = f_c exp(L' - log Y), L' = (B_K - max B_K) s + sum w_i D_i,
 // s = log(contrast) / (max B_K - min B_K); L = log(Y scale), so exp(-log Y) =
-// scale exp(-L).  mm: the partial minima and maxima of B_K.  out may be f,
+// scale exp(-L); where exp(L' - L) is near the ends of float32, scale joins
+// the exponent, since their product need not be.  mm: the partial minima and maxima of B_K.  out may be f,
 // and L and the levels may lie in out: every value at i is read first.
 constexpr int kMaxScales = 4;
 struct ToneArgs {
@@ -218,7 +219,7 @@ __global__ void __launch_bounds__(kThreads) k_tonemap(const float* f, const floa
   };
   if (i < plane) load();  // in flight during the reduction of the partials
   float bmin = mm[2 * threadIdx.x], bmax = mm[2 * threadIdx.x + 1];
-  const float k = *scale;
+  const float k = *scale, lk = logf(k);
   block_minmax(bmin, bmax);
   const float s = bmax > bmin ? log_contrast / (bmax - bmin) : 1.0f;
   while (i < plane) {
@@ -231,7 +232,8 @@ __global__ void __launch_bounds__(kThreads) k_tonemap(const float* f, const floa
           acc = fmaf(a.w[q], prev - b[q].v[e], acc);
           prev = b[q].v[e];
         }
-      const float g = k * expf(fmaf(prev - bmax, s, acc) - l.v[e]);
+      const float x = fmaf(prev - bmax, s, acc) - l.v[e];
+      const float g = fabsf(x) < 80.0f ? k * expf(x) : expf(x + lk);
 #pragma unroll
       for (int q = 0; q < 3; ++q) c[q].v[e] *= g;
     }
