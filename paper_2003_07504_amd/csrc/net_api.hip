@@ -727,11 +727,49 @@ hipError_t run_forward(ils_net* n, const float* f, const float* lam, const float
 // the cheapest number, the chip taking its blocks in rounds.  At least 16 are
 // looked at: 16 frames of 1080p are 576 strips, which whole (2 1/4 rounds) took
 // 3670 us and in four segments each (9 rounds) take 2780.
+struct StreamPlan {
+  int strips, segs;
+  long long rounds, steps;  // of one launch, and of one of its rounds
+};
+StreamPlan stream_plan(int B, int H, int W, int cus) {
+  StreamPlan s{(W + SW - 1) / SW, 1, 1, 0};
+  const long long units = (long long)B * s.strips;
+  for (int g = 1; g <= (H + 1) / 2 && (g <= 16 || units * g <= 4LL * cus); ++g) {
+    const long long rounds = (units * g + cus - 1) / cus;
+    const long long steps = ((H + g - 1) / g + 1) / 2 + 12;
+    if (g > 1 && rounds * steps >= s.rounds * s.steps) continue;
+    s.segs = g;
+    s.rounds = rounds;
+    s.steps = steps;
+  }
+  return s;
+}
+
+// Whether the network runs faster layer by layer than as strips: for many
+// images of few rows, where the pipeline's 12 steps are most of a segment's, or
+// of a few columns or a little over one strip's.  Both times in microseconds,
+// fitted to 780 sizes of 1 to 512 images of 2 to 64 rows and 2 to 256 columns
+// (per compute unit: tiles and pixels of the layers, of which images smaller
+// than a tile take the halo by division): strips within 7 %, layers within 11.
+// Over 320 further sizes up to 8 M pixels the choice is within 6 % of the faster
+// one; strips alone took up to 1.5 times the layers' time.  267 images of 327 x
+// 5: strips 457 us, layers 299; 512 of 8 x 55: 91, 75; of 32 x 55: 191, 171; of
+// 64 x 64: 221, 262; one 256 x 256: 19, 34; 8 of 720 x 1280: 650, 1222.
+bool stream_loses(const StreamPlan& s, int B, int H, int W, int cus) {
+  const double strips = s.rounds * (1.97 * s.steps - 9.7) + 1.3;
+  const double tiles = (double)B * ((H + TH - 1) / TH) * ((W + TW - 1) / TW) / cus;
+  const double full = (double)B * H * W / ((double)TH * TW * cus);  // tiles' worth of pixels
+  const bool near = H >= TH + 2 && W >= TW + 2;
+  const double layers = near ? 30.0 + 5.25 * tiles + 4.44 * full : 36.0 + 6.06 * tiles + 3.76 * full;
+  return strips > 1.02 * layers;
+}
+
 // In place, where other strips' halos would be overwritten, layer by layer.
 hipError_t run_stream(ils_net* n, const float* f, const float* lam, const float* p, int B, int H, int W, float* v) {
   const size_t vals = (size_t)B * 3 * H * W;
-  if (f < v + vals && v < f + vals) return run_forward(n, f, lam, p, B, H, W, v);
   static const int cus = resident_blocks(reinterpret_cast<const void*>(&k_net_stream), 512);
+  const StreamPlan sp = stream_plan(B, H, W, cus);
+  if ((f < v + vals && v < f + vals) || stream_loses(sp, B, H, W, cus)) return run_forward(n, f, lam, p, B, H, W, v);
   StreamArgs a{};
   a.f = f;
   a.lam = lam;
@@ -743,19 +781,9 @@ hipError_t run_stream(ils_net* n, const float* f, const float* lam, const float*
   }
   a.H = H;
   a.W = W;
-  a.strips = (W + SW - 1) / SW;
-  const long long units = (long long)B * a.strips;
-  a.segs = 1;
-  long long best = -1;
-  for (int g = 1; g <= (H + 1) / 2 && (g <= 16 || units * g <= 4LL * cus); ++g) {
-    const long long rounds = (units * g + cus - 1) / cus;
-    const long long cost = rounds * (((H + g - 1) / g + 1) / 2 + 12);
-    if (best < 0 || cost < best) {
-      best = cost;
-      a.segs = g;
-    }
-  }
-  hipLaunchKernelGGL(k_net_stream, dim3((unsigned)(units * a.segs)), dim3(512), 0, n->stream, a);
+  a.strips = sp.strips;
+  a.segs = sp.segs;
+  hipLaunchKernelGGL(k_net_stream, dim3((unsigned)((long long)B * sp.strips * sp.segs)), dim3(512), 0, n->stream, a);
   return hipGetLastError();
 }
 
