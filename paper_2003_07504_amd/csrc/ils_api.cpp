@@ -20,6 +20,7 @@
 #include "../../include/ils.h"
 #include "ils_launch.hpp"
 #include "ils_scale.hpp"
+#include "ils_tune.hpp"
 
 using ilsk::WorkList;
 using ilsk::cf;
@@ -393,11 +394,12 @@ hipError_t ilsk_launch_tonemap(const float* f, const float* L, const float* cons
                                hipStream_t st);
 
 // ---------------------------------------------------------------- tuner
-// Lengths of 480 and more offer two row-band and two column-tile shapes.
+// Lengths of 480 and more offer up to six row-band and four column-tile shapes.
 // The first call for an image size times each shape on the plan's stream
-// (HIP events, a few launches on workspace data, so it synchronises once)
-// and keeps the faster; the choice does not change any result bit, since
-// every row and column goes through the same arithmetic in either shape.
+// (HIP events, a few launches on workspace data, so it synchronises) and keeps
+// the fastest, or a preferred one of those that are as fast (ils_tune.hpp); the
+// choice does not change any result bit, since every row and column goes
+// through the same arithmetic in any shape.
 // ILS_TUNE=0 keeps the default shapes; ILS_TUNE_CACHE names a text file of
 // earlier choices ("arch H W C row col" per line) that is read at plan
 // creation and appended to.
@@ -439,21 +441,33 @@ static void load_tune_cache(ils_plan* plan) {
   std::fclose(fh);
 }
 
-// Milliseconds of two launches (the better of two runs after a warm one; a
-// first call pays for every shape's timing, and four runs chose no better).
-static float time_launches(ils_plan* plan, const std::function<hipError_t()>& launch) {
-  hipEvent_t ev[3] = {};
-  bool ok = launch() == hipSuccess;
-  for (hipEvent_t& e : ev) ok = ok && hipEventCreate(&e) == hipSuccess;
-  ok = ok && hipEventRecord(ev[0], plan->stream) == hipSuccess;
-  for (int rep = 1; rep <= 2; ++rep)
-    ok = ok && launch() == hipSuccess && launch() == hipSuccess && hipEventRecord(ev[rep], plan->stream) == hipSuccess;
-  ok = ok && hipEventSynchronize(ev[2]) == hipSuccess;
-  float a = 0.0f, b = 0.0f;
-  ok = ok && hipEventElapsedTime(&a, ev[0], ev[1]) == hipSuccess && hipEventElapsedTime(&b, ev[1], ev[2]) == hipSuccess;
-  for (hipEvent_t e : ev)
-    if (e) (void)hipEventDestroy(e);
-  return ok ? std::min(a, b) : -1.0f;
+// Milliseconds of two launches of each of n <= kMaxShapes shapes (negative where
+// the timing failed): every shape runs once to warm up, then all are timed in
+// turn, twice, and the better time counts, so that a clock still rising on a
+// first call favours none.  Synchronises once.
+static void time_shapes(ils_plan* plan, int n, const std::function<hipError_t(int)>& launch, float* ms) {
+  constexpr int kReps = 2;
+  hipEvent_t ev[kReps][ilsk::kMaxShapes + 1] = {};
+  bool ok = true;
+  for (int v = 0; v < n; ++v) ok = ok && launch(v) == hipSuccess;
+  for (auto& rep : ev) {
+    for (int v = 0; v <= n; ++v) ok = ok && hipEventCreate(&rep[v]) == hipSuccess;
+    ok = ok && hipEventRecord(rep[0], plan->stream) == hipSuccess;
+    for (int v = 0; v < n; ++v)
+      ok = ok && launch(v) == hipSuccess && launch(v) == hipSuccess && hipEventRecord(rep[v + 1], plan->stream) == hipSuccess;
+  }
+  ok = ok && hipEventSynchronize(ev[kReps - 1][n]) == hipSuccess;
+  for (int v = 0; v < n; ++v) {
+    ms[v] = -1.0f;
+    for (auto& rep : ev) {
+      float t = 0.0f;
+      ok = ok && hipEventElapsedTime(&t, rep[v], rep[v + 1]) == hipSuccess;
+      if (ok && (ms[v] < 0.0f || t < ms[v])) ms[v] = t;
+    }
+  }
+  for (auto& rep : ev)
+    for (hipEvent_t e : rep)
+      if (e) (void)hipEventDestroy(e);
 }
 
 // A frame with a row or column length that has no compiled split runs
@@ -535,24 +549,21 @@ static Pick choose(ils_plan* plan, const FrameDesc& d) {
       FrameDesc t = d;
       t.f = t.u0 = reinterpret_cast<const float*>(t.specB);
       t.out = reinterpret_cast<float*>(t.specB);
-      float bestr = 1e30f, bestc = 1e30f;
+      float ms[ilsk::kMaxShapes];
+      int rows[ilsk::kMaxShapes];
+      WorkList wl[ilsk::kMaxShapes];
       for (int v = 0; v < orow->nrow; ++v) {
+        rows[v] = orow->row[v].rows[ilsk::ROW_MID];
         const FrameDesc tb = banded(plan->cus, &orow->row[v], t);
-        const WorkList wl = one_frame(tb, row_items(&orow->row[v], ilsk::ROW_MID, tb));
-        const float ms = time_launches(plan, [&] { return orow->row[v].launch(ilsk::ROW_MID, ilsk::PEN_CHARBONNIER, wl, plan->stream); });
-        if (ms >= 0.0f && ms < bestr) {
-          bestr = ms;
-          ch.first = v;
-        }
+        wl[v] = one_frame(tb, row_items(&orow->row[v], ilsk::ROW_MID, tb));
       }
-      for (int v = 0; v < ocol->ncol; ++v) {
-        const WorkList wl = one_frame(t, col_items(&ocol->col[v], t));
-        const float ms = time_launches(plan, [&] { return ocol->col[v].launch(wl, plan->stream); });
-        if (ms >= 0.0f && ms < bestc) {
-          bestc = ms;
-          ch.second = v;
-        }
-      }
+      time_shapes(plan, orow->nrow, [&](int v) {
+        return orow->row[v].launch(ilsk::ROW_MID, ilsk::PEN_CHARBONNIER, wl[v], plan->stream);
+      }, ms);
+      ch.first = ilsk::pick_row(ms, rows, orow->nrow);
+      for (int v = 0; v < ocol->ncol; ++v) wl[v] = one_frame(t, col_items(&ocol->col[v], t));
+      time_shapes(plan, ocol->ncol, [&](int v) { return ocol->col[v].launch(wl[v], plan->stream); }, ms);
+      ch.second = ilsk::pick_col(ms, ocol->ncol);
       const char* path = std::getenv("ILS_TUNE_CACHE");
       if (path) {
         FILE* fh = std::fopen(path, "a");
