@@ -43,9 +43,10 @@ def step_bytes(H, W, C, N):
     return b["row_first"] + (N - 1) * b["row_mid"] + N * b["column"] + b["row_final"]
 
 
-def profile_entry(kernel, H, W, C):
+def profile_entry(kernel, H, W, C, shapes):
     """Counter figures per launch measured with rocprofv3 (committed under
-    profiles/), or None when absent or taken on a different kernel source."""
+    profiles/), or None when absent or taken on a different kernel source or
+    on other tile shapes than [row, column] `shapes`."""
     path = os.path.join(ROOT, "profiles", "traffic.json")
     if not os.path.exists(path):
         return None
@@ -53,22 +54,22 @@ def profile_entry(kernel, H, W, C):
         t = json.load(fh)
     e = t.get(f"{kernel}@{H}x{W}x{C}")
     from paper_2003_07504_amd.build import source_hash
-    if not e or e.get("source_hash") != source_hash() or "bytes_per_launch" not in e:
+    if not e or e.get("source_hash") != source_hash() or "bytes_per_launch" not in e or e.get("shapes") != shapes:
         return None
     return e
 
 
-def roofline_of(kernel, avg_us, alg_bytes, H, W, C):
+def roofline_of(kernel, avg_us, alg_bytes, H, W, C, shapes):
     """Roofline of the dominant kernel against HBM: algorithmic bytes per
     launch (20N+4 model, per pass kind) / the kernel's average launch
     duration (events around a run of un-bracketed launches) / 8 TB/s.
     `traffic` is the measured HBM bytes per launch (FETCH_SIZE + WRITE_SIZE,
     scaled by a copy of known size) when the committed counter file was taken
-    on the current kernel sources, else null.  The kernel's vector issue rate
+    on the current kernel sources and tile shapes, else null.  The kernel's vector issue rate
     (SQ_INSTS_VALU x 64 lanes against 256 CUs x 64 lanes x 2.4 GHz, packed
     FP32 off) is reported beside it as `alu`."""
     ach = alg_bytes / (avg_us * 1e-6) / 1e9
-    e = profile_entry(kernel, H, W, C)
+    e = profile_entry(kernel, H, W, C, shapes)
     out = {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": e["bytes_per_launch"] if e else None,
            "kernel": kernel, "avg_launch_us": avg_us, "alg_bytes_per_launch": alg_bytes}
@@ -586,7 +587,7 @@ def main():
         raise RuntimeError("HIP error during pass timing")
     dom = max(per_kind, key=lambda k: per_kind[k]["avg_us"] * per_kind[k]["per_step"])
     dk = per_kind[dom]
-    roofline = roofline_of(dom, dk["avg_us"], dk["alg_bytes"], H, W, C)
+    roofline = roofline_of(dom, dk["avg_us"], dk["alg_bytes"], H, W, C, list(shapes.values()))
     step_alg = step_bytes(H, W, C, N)
 
     if args.copy_ref:  # a copy of known size, to scale the profiler's byte counters

@@ -1,14 +1,17 @@
 """Summarise rocprofv3 output (rocpd SQLite databases) of a bench.py run.
 
     python -m paper_2003_07504_amd.rocprof_summary --trace KT.db --fetch F.db \
-        --write W.db [--sq S.db] --size 1080x1920x3 --command "<rocprofv3 ...>" \
-        --out profiles/ils_passes_1080p_rgb_n4.txt
+        --write W.db [--sq S.db] --size 1080x1920x3 --shapes 2,0 \
+        --command "<rocprofv3 ...>" --out profiles/ils_passes_1080p_rgb_n4.txt
+
+All runs have to use the same tile shapes: give them one ILS_TUNE_CACHE file
+(the first run writes it; the others then time no shapes either).
 
 Writes a short text summary (per-kernel call counts and durations, HBM bytes
 per launch from FETCH_SIZE / WRITE_SIZE scaled by what the same counters
 read for a 512 MiB device copy, SQ counters) and records the bytes per
-launch in profiles/traffic.json under the current kernel-source hash, which
-bench.py uses for the roofline's `traffic` field.
+launch in profiles/traffic.json under the current kernel-source hash and the
+tile shapes, which bench.py uses for the roofline's `traffic` field.
 """
 from __future__ import annotations
 
@@ -108,14 +111,10 @@ def copy_ref(db, counter):
 
 
 def by_kind(cnt, kt, kind):
-    """Counters of the kernel instance the trace chose for this kind (the copy
-    reference is looked up by kind)."""
-    if kind in kt and kt[kind][0] in cnt:
-        return cnt[kt[kind][0]]
-    for name, v in cnt.items():
-        if kind_of(name) == kind:
-            return v
-    return {}
+    """Counters of the kernel instance the trace chose for this kind; none if
+    the counter run did not launch that instance (another tile shape is
+    another kernel, with other counts)."""
+    return cnt.get(kt[kind][0], {}) if kind in kt else {}
 
 
 def main():
@@ -125,6 +124,7 @@ def main():
     ap.add_argument("--write", required=True)
     ap.add_argument("--sq", default=None)
     ap.add_argument("--size", required=True, help="HxWxC of the profiled workload")
+    ap.add_argument("--shapes", default="0,0", help="row and column shape index of the runs (bench.py's tile_shapes)")
     ap.add_argument("--iters", type=int, default=4, help="N of the profiled workload")
     ap.add_argument("--command", required=True, help="the rocprofv3 command line that produced the data")
     ap.add_argument("--out", required=True)
@@ -142,7 +142,7 @@ def main():
     spec = C * H * (W // 2 + 1) * 8
     alg = {"row_first": img + spec, "row_mid": img + 2 * spec, "row_final": img + spec, "column": 2 * spec}
     lines = [f"# rocprofv3 summary: ILS passes, {W}x{H}x{C} float32, N={a.iters}", "",
-             f"command: {a.command}", f"kernel source hash: {source_hash()}",
+             f"command: {a.command}", f"kernel source hash: {source_hash()}; row, column shape {a.shapes}",
              f"counter scale from a {COPY_BYTES >> 20} MiB copy: FETCH_SIZE x{fscale:.4f}, WRITE_SIZE x{wscale:.4f}",
              "", f"{'pass':10s} {'calls':>5s} {'avg_us':>8s} {'min_us':>8s} {'max_us':>8s} "
                  f"{'alg_MB':>8s} {'hbm_MB':>8s} {'rd_MB':>8s} {'wr_MB':>8s} {'alg_GB/s':>9s} {'hbm_GB/s':>9s}"]
@@ -154,12 +154,16 @@ def main():
         if k not in kt:
             continue
         name, calls, avg, lo, hi = kt[k]
-        rd = by_kind(fe, kt, k).get("FETCH_SIZE", 0.0) * 1024 * fscale
-        wb = by_kind(wr, kt, k).get("WRITE_SIZE", 0.0) * 1024 * wscale
+        fk, wk = by_kind(fe, kt, k), by_kind(wr, kt, k)
+        if not fk or not wk:
+            raise SystemExit(f"{k}: the counter runs did not launch {name}; use one ILS_TUNE_CACHE for all runs")
+        rd = fk["FETCH_SIZE"] * 1024 * fscale
+        wb = wk["WRITE_SIZE"] * 1024 * wscale
         lines.append(f"{k:10s} {calls:5d} {avg:8.3f} {lo:8.3f} {hi:8.3f} {alg[k] / 1e6:8.2f} {(rd + wb) / 1e6:8.2f} "
                      f"{rd / 1e6:8.2f} {wb / 1e6:8.2f} {alg[k] / (avg * 1e3):9.1f} {(rd + wb) / (avg * 1e3):9.1f}")
         traffic[f"{k}@{a.size}"] = {"bytes_per_launch": int(rd + wb), "read_bytes": int(rd), "write_bytes": int(wb),
-                                    "source_hash": source_hash(), "kernel": name}
+                                    "source_hash": source_hash(), "kernel": name,
+                                    "shapes": [int(v) for v in a.shapes.split(",")]}
     tl = timeline(a.trace, kt, 2 * a.iters + 1)
     if tl:
         span, busy, gaps, n = tl
@@ -172,7 +176,7 @@ def main():
             sk = by_kind(sq, kt, k)
             if sk:
                 lines.append(f"  {k}: " + ", ".join(f"{cn}={v:.0f}" for cn, v in sorted(sk.items())))
-                traffic.setdefault(f"{k}@{a.size}", {})["sq"] = dict(sk)
+                traffic[f"{k}@{a.size}"]["sq"] = dict(sk)
     with open(a.out, "w") as fh:
         fh.write("\n".join(lines) + "\n")
     with open(a.traffic, "w") as fh:
