@@ -414,6 +414,8 @@ static long long size_key(int H, int W, int C) {
   return ((long long)H << 48) | ((long long)W << 32) | (long long)(unsigned)C;
 }
 
+static_assert(ILS_MAX_SCALES <= ilsk::kMaxLevels, "LevelLists holds the levels of a call in at most two groups");
+
 // Sizes whose shapes the tuner times; others with compiled passes take a
 // shape by rule (rule_pick).
 static bool tuned_size(int H, int W) {

@@ -196,7 +196,7 @@ __global__ void __launch_bounds__(kThreads) k_minmax_partial(const float* __rest
 // scale exp(-L); where exp(L' - L) is near the ends of float32, scale joins
 // the exponent, since their product need not be.  mm: the partial minima and maxima of B_K.  out may be f,
 // and L and the levels may lie in out: every value at i is read first.
-constexpr int kMaxScales = 4;
+constexpr int kMaxScales = ILS_MAX_SCALES;
 struct ToneArgs {
   const float* B[kMaxScales];
   float w[kMaxScales];
