@@ -188,7 +188,9 @@ int ils_tone_map(ils_plan* plan, const float* f, int H, int W, float lambda, flo
  * is kept up to a shift.  1 <= K <= ILS_MAX_SCALES; weights (host array)
  * finite and >= 0; contrast > 1.  The workspace must hold
  * ils_tone_map_multiscale_workspace_bytes(H, W, K) (the spectra of one
- * channel and K + 1 luminance planes).  out == f allowed. */
+ * channel and K + 1 luminance planes); when it holds the spectra of K (or two)
+ * channels, several levels run at once.  out is used as scratch before the
+ * result is written.  out == f allowed. */
 #define ILS_MAX_SCALES 4
 size_t ils_tone_map_multiscale_workspace_bytes(int max_H, int max_W, int K);
 int ils_tone_map_multiscale(ils_plan* plan, const float* f, int H, int W, const float* lambdas,
@@ -273,19 +275,22 @@ int ils_last_error(ils_plan* plan);
  * same arithmetic on every row and column, so the results are bitwise equal;
  * only the speed differs.  The first smoothing call for a size H x W x C
  * times the shapes on the plan's stream (a few launches on workspace data,
- * one host synchronisation) and keeps the faster ones for the plan's life.
+ * two host synchronisations) and keeps the fastest ones for the plan's life, or
+ * a preferred one of those that are as fast, so that plans choose alike.
  * A call made while the stream is being captured into a graph keeps the
  * default shapes and leaves the size untuned.  A row shape's height is the
  * most rows a workgroup holds: a single frame's rows are cut into balanced
  * bands of at most that many rows, as many as fill whole rounds of the
  * compute units.  In ils_smooth_batch, frames large enough to be parts of
- * their own take the widest column tile.  Environment: ILS_TUNE=0
+ * their own take the default column tile.  Environment: ILS_TUNE=0
  * keeps the defaults; ILS_TUNE_CACHE=<file> reads earlier choices at plan
  * creation ("arch H W C rows-per-band columns-per-tile" per line) and
  * appends new ones.
  *
  * ils_shape_variants: number of row / column shapes for a supported size
- *   (1 to 6 and 1 to 4; 1 and 1 for a frame on the runtime-length passes).
+ *   (1 to 6 and 1 to 4; 1 and 1 for a frame whose shapes are not timed: on
+ *   the runtime-length passes, or with a length that has one row shape, whose
+ *   column tile follows from a rule).
  *   ILS_ERR_UNSUPPORTED_SIZE otherwise.
  * ils_plan_tune: tune the size now if it is not yet (synchronises the
  *   plan's stream) and return the chosen shape indices (0 = default).

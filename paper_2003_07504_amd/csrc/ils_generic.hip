@@ -16,8 +16,8 @@
 //   final  : c2r(spectrum)         -> out
 // i.e. 28 bytes per pixel-channel per iteration instead of the fused
 // passes' 20.  The scale conventions are those of the compiled passes: the
-// row transform leaves a factor 2 and the column pass multiplies by
-// 1 / (2 H W).
+// row transform leaves a factor 2, the column pass multiplies by s / (2 H W) and
+// the final pass by 1 / s (FrameDesc::u_scale).
 #include "ils_launch.hpp"
 
 namespace ilsk {
@@ -183,7 +183,7 @@ __global__ void __launch_bounds__(kGenThreads) k_gen_c2r(WorkList wl) {
 }
 
 // Column pass on S columns of the second half spectrum, in place: forward
-// column DFT, times 1 / (2 H W (1 + kappa (Sx[k] + Sy[l]))) (Eq. (9)
+// column DFT, times s / (2 H W (1 + kappa (Sx[k] + Sy[l]))) (Eq. (9)
 // denominator), inverse column DFT.  H * S <= kGenColCf.
 template <int S>
 __global__ void __launch_bounds__(kGenThreads) k_gen_col(WorkList wl) {

@@ -107,10 +107,15 @@ struct RowGeom {
   static constexpr int NPAIR = (M / 2 + 1 + T - 1) / T;  // (k, M-k) pairs per lane of the real-FFT pre/post-process
 };
 
-// LDS that co-resident workgroups of one kernel may take on a CU in all.  A
-// single workgroup may use the whole 160 KB, but two are placed on one CU
-// only when each takes at most about 77 KB (measured on MI355X: two blocks
-// of 77 280 B run side by side, two of 79 200 B do not).
+// LDS that co-resident workgroups of one kernel are planned to take in all.  A
+// CU has 160 KB and gives them out in pieces of 1280 B (measured: two blocks of
+// 81 920 B, three of 53 760, four of 40 960 or five of 32 000 run side by side,
+// one byte more and one fewer do).  Planning with 154 560 B instead counts one
+// block per CU for tiles of 77 281 to 81 920 B: with all of the 160 KB, tables
+// move in and out of the LDS and kernels are compiled for more waves, which
+// over 24 column heights and six workloads was up to 20 % faster (8 RGB frames
+// of 225 x 640) and up to 17 % slower (4 of 256 x 1280; lone grey ones of 1728
+// and 1800 x 640 8 %, while 1600 and 2400 gained 6).
 constexpr int kLdsCoresident = 154560;
 constexpr int resident_blocks(int lds_bytes) {
   return lds_bytes * 2 > kLdsCoresident ? 1 : kLdsCoresident / lds_bytes;
@@ -590,7 +595,8 @@ __device__ __forceinline__ void row_body(const FrameDesc& d, int band, int ch, f
 
 // --------------------------------------------------------------------------
 // Row pass, mode FINAL: C2R of G rows, written to the output image.
-// Block = G slots x T lanes; slot s holds row y0 + s.
+// Block = (G + 2) slots x T lanes, the bands of the other passes; slot s holds
+// row y0 + s, the last two none.
 // --------------------------------------------------------------------------
 template <int P, int Q, int G>
 __device__ __forceinline__ void row_final_body(const FrameDesc& d, int band, int ch, float* smem) {
@@ -771,14 +777,20 @@ __device__ __forceinline__ void col_body(const FrameDesc& d, int tile, int ch, f
 }
 
 // --------------------------------------------------------------------------
-// Column pass of lengths 400 .. 1000 in three stages, H = R1 R2 R3 with
-// factors of at most 16: a lane holds a third to a half of the two-stage
-// pass's values, so that the chain of instructions a single tile waits for
-// is short.  Frames of up to a few blocks per CU gain (480p RGB 6.5 -> 5.3
-// us, 720p grey 7.5 -> 6.1, RGB 9.9 -> 8.8), full chips stay as they are
-// (12 x 720p 24.2 -> 24.1); longer columns lose it again to the narrower
-// tiles (1080p RGB 16.4 -> 17.2), shorter ones to the extra exchange (96 x
-// 256 x 256: 10 -> 14).
+// Column pass of lengths 400 .. 1000 (not 625, which has no such split, nor 675
+// and 750, whose smallest factor of 5 would need more than 1024 lanes) in three
+// stages, H = R1 R2 R3 with factors of at most 16: a lane holds a quarter to a
+// half of the two-stage pass's values, so that the chain of instructions a
+// single tile waits for is short.  Whole frames, N = 4, against two stages: one
+// of H x 800 grey 7 to 12 % faster at every height (480: 68.3 -> 64.0 us, 1000:
+// 88.2 -> 77.8), RGB 3 to 7 %; one of H x 1600 RGB from 14 % faster (972) to 5 %
+// slower (900); four of H x 800 RGB from 8 % faster to 3 % slower; four of H x
+// 1600 RGB, which fill the chip, from 5 % faster (576, 640) to 5 % slower (400,
+// 450, 512, 540, 864), 500 and 600, whose splits leave half the lanes idle in
+// two stages, 15 and 12 % slower (245 -> 282 us, 268 -> 301).  (A length has one
+// form: a batch gives the bits of its frames.)  Longer columns lose it to the
+// narrower tiles (1080p RGB 16.4 -> 17.2 us a pass), shorter ones to the extra
+// exchange (96 x 256 x 256: 10 -> 14).
 //   n = n1 R2 R3 + n2 R3 + n3,  k = k1 + R1 k2 + R1 R2 k3:
 // stage 1 over n1 (lane (n2, n3)), twiddle W_H^(k1 (n2 R3 + n3)); stage 2
 // over n2 (lane (k1, n3)), twiddle W_(R2 R3)^(k2 n3); stage 3 over n3 (lane

@@ -367,8 +367,9 @@ __global__ void __launch_bounds__(256) k_wgrad_first(const bf16* g, const bf16* 
 // as one 201 MB), and held twice in LDS: pixel by pixel as the operand of
 // the convolution, channel by channel as that of the weight gradient, of which
 // row p of x meets rows p .. p + 2.  x lies there channel by channel too, and
-// pixel by pixel as the mask.  79 KB: two blocks per CU, so that one's loads
-// and stores run beside the other's products.  Two waves share rows and halve
+// pixel by pixel as the mask.  80 256 B, of which two blocks fit a CU's 160 KB
+// (8 tiles a block: 256 blocks 45.5 us, 512 56.9), so that one's loads and
+// stores run beside the other's products.  Two waves share rows and halve
 // the channels of the convolution, which leaves its weights 36 registers; with
 // 72 the kernel spilled and took 78 us.  A 32-channel layer of those crops
 // took 40 us for the gradient of x and 41 for that of the weights; this takes
