@@ -482,7 +482,12 @@ static bool frame_generic(int H, int W) { return !find_ops(W / 2) || !find_ops(H
 // four rows (or the shape's height, if less).  The blocks of a round then
 // end together instead of the last round running a few blocks alone.  Two
 // blocks of a shape count as resident on one CU when its LDS allows it and
-// a block has at most four waves (one wave of each per SIMD).  The
+// a block has at most four waves (one wave of each per SIMD).  Bands of long
+// rows (W of 1200 and more, sizes without timed shapes) go down to one row where
+// the frame has no more rows in all than the chip has compute units: a block
+// holds few waves a row, so its time grows with its rows, while the halo costs
+// idle units only (N = 4, grey: 5 x 5000 146 -> 111 us, 117 on the runtime-length
+// passes; 30 x 2500 102 -> 91, 93; shorter rows lose up to 9 %).  The
 // runtime-length kernels keep their own bands.
 static FrameDesc banded(int cus, const RowVariant* v, FrameDesc d) {
   d.nb_row = 0;
@@ -492,7 +497,8 @@ static FrameDesc banded(int cus, const RowVariant* v, FrameDesc d) {
   const int per_cu = (v->threads + 63) / 64 <= 4 ? ilsk::resident_blocks(v->lds_bytes) : 1;
   const long long per_round = (long long)cus * per_cu;
   const long long rounds = ((long long)d.C * lo + per_round - 1) / per_round;
-  const int hi = std::max(lo, d.H / std::min(g, 4));
+  const bool few = d.H >= 4 && d.W >= 1200 && (long long)d.C * d.H <= cus && !tuned_size(d.H, d.W);
+  const int hi = std::max(lo, d.H / (few ? 1 : std::min(g, 4)));
   d.nb_row = (int)std::max<long long>(lo, std::min<long long>(rounds * per_round / d.C, hi));
   return d;
 }
