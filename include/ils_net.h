@@ -36,7 +36,9 @@ typedef struct ils_net ils_net;
 int ils_net_param_count(void);
 
 /* Device workspace bytes for batches up to max_B images of max_H x max_W
- * (activations, gradients, parameters, optimiser state).  0 if invalid. */
+ * (activations, gradients, parameters, optimiser state).  0 if invalid.  Up to
+ * 9.5 MB more are used for the gradients' partial sums (faster for many images
+ * smaller than 8 x 32). */
 size_t ils_net_workspace_bytes(int max_B, int max_H, int max_W);
 
 /* Create a network on caller-owned workspace (256-byte aligned, at least

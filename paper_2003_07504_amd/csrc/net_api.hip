@@ -623,16 +623,18 @@ size_t net_layout(int B, int H, int W, ils_net* n) {
   o_act[0] = take(px * 8 * 2);
   for (int i = 1; i < 5; ++i) o_act[i] = take(px * 32 * 2);
   size_t o_gb0 = take(px * 32 * 2), o_gb1 = take(px * 32 * 2);
+  size_t o_lp = take(kLossBlocks * 8);
+  size_t o_loss = take(4);
   // The last activation, v and the partial sums lie together: behind layer 5
   // the first two are spent, and the partial sums of the layers before it
   // start where they did, so that kWgradBlocks rows of a 32 -> 32 layer fit
-  // an area of kPartialRows of them for any batch of so many full tiles.
+  // an area of kPartialRows of them for any batch of so many full tiles.  The
+  // partial sums end the workspace and take what it holds beyond the minimum:
+  // many images smaller than a tile have more tiles than the minimum has rows
+  // (64 crops of 9 x 93: 183 us with it, 167 with kWgradBlocks rows).
   o_act[5] = take(px * 32 * 2);
   size_t o_z = take(px * 3 * 4);
   size_t o_part = take((size_t)kPartialRows * (32 * 32 * 9 + 32) * 4);
-  const size_t e_part = off;
-  size_t o_lp = take(kLossBlocks * 8);
-  size_t o_loss = take(4);
   if (n) {
     char* b = n->ws;
     n->master = (float*)(b + o_master);
@@ -649,9 +651,9 @@ size_t net_layout(int B, int H, int W, ils_net* n) {
     n->gbuf[1] = (bf16*)(b + o_gb1);
     n->zbuf = (float*)(b + o_z);
     n->partial = (float*)(b + o_part);
-    n->partial_bytes = e_part - o_part;
+    n->partial_bytes = n->ws_bytes - o_part;
     n->partial_wide = (float*)(b + o_act[5]);
-    n->partial_wide_bytes = e_part - o_act[5];
+    n->partial_wide_bytes = n->ws_bytes - o_act[5];
     n->lpart = (double*)(b + o_lp);
     n->loss = (float*)(b + o_loss);
   }

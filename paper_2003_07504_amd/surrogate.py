@@ -116,6 +116,8 @@ class Net:
         nbytes = int(self._lib.ils_net_workspace_bytes(max_B, max_H, max_W))
         if nbytes == 0:
             raise ValueError("invalid network limits")
+        # room for another 256 blocks' partial sums of the largest layer
+        nbytes += 256 * 4 * max(layer_param_sizes())
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         h = ctypes.c_void_p()
         check(self._lib.ils_net_create(ctypes.byref(h), max_B, max_H, max_W,

@@ -18,10 +18,12 @@ def test_workspace_size_is_what_it_was(B, H, W, nbytes):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("least", [True, False])
 @pytest.mark.parametrize("B,H,W", [(512, 2, 2), (300, 9, 33)])
-def test_gradients_with_fewer_rows_than_tiles(B, H, W):
-    """More tiles than rows of partial sums fit.  Bound as in the other
-    gradient tests: bf16 rounding of the backward values, six layers deep."""
+def test_gradients_with_fewer_rows_than_tiles(monkeypatch, B, H, W, least):
+    """More tiles than rows of partial sums fit the least workspace, and the
+    binding's own, which holds a row per tile.  Bound as in the other gradient
+    tests: bf16 rounding of the backward values, six layers deep."""
     import torch
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
@@ -34,7 +36,11 @@ def test_gradients_with_fewer_rows_than_tiles(B, H, W):
     p = rng.uniform(0.5, 1.0, B).astype(np.float32)
     t = np.clip(f + 0.05 * rng.standard_normal(f.shape), 0, 1).astype(np.float32)
     flat = 3.0 * S.init_params(seed=7)
+    if least:
+        monkeypatch.setattr(S, "layer_param_sizes", lambda: [0])
     net = S.Net(B, H, W, params=flat)
+    monkeypatch.undo()
+    assert (net.workspace.numel() == S._lib().ils_net_workspace_bytes(B, H, W)) == least
     g, loss = net.gradients(*(torch.from_numpy(v).cuda() for v in (f, lam, p, t)))
     torch.cuda.synchronize()
     g = g.cpu().numpy().astype(np.float64)
